@@ -75,9 +75,9 @@ enum fft_status {
  *   n          transform length, a power of two in [256, 1048576].  Up to
  *              16384 a whole transform fits in one CU's LDS and a single-pass
  *              kernel is available; above it only the four-step (eq. (3),
- *              Section IV-D rule 3) exists: N1 x 16384 with N1 <= 64, or
- *              N1 x N2 with N1, N2 in {256, 512, 1024}, whichever the tuned
- *              table names for (n, batch).
+ *              Section IV-D rule 3) exists: N1 x 16384 with N1 <= 64, or the
+ *              column splits N1 x N2 with N1, N2 in {128, 256, 512, 1024},
+ *              whichever the tuned table names for (n, batch).
  *   batch      number of rows, >= 1.
  *   direction  FFT_FORWARD or FFT_BACKWARD.
  * The plan owns device memory for its twiddle tables (computed in FP64 on
@@ -366,7 +366,9 @@ int fft_set_launch_limit(int64_t max_groups);
  *   shapes that exchange through the LDS only).
  * fft_variant_twiddles: the FP32 twiddle table of variant `index` as built
  *   for the device (interleaved re, im; forward direction), written into
- *   out[0 .. 2*count); *count receives the number of complex entries.
+ *   out[0 .. 2*count); *count receives the number of complex entries.  The
+ *   column splits above 16384 hold the same roots, each rounded once, in
+ *   their kernels' own order; this call gives the two-level form for them.
  *   With out == NULL only *count is set.
  * fft_plan_describe: JSON text describing a plan: its variant, and for a
  *   single-pass variant "variant_resources" (VGPRs, scratch bytes per lane,

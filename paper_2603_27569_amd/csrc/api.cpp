@@ -14,6 +14,7 @@
 #include <mutex>
 #include <string>
 #include <unordered_set>
+#include <utility>
 #include <vector>
 
 #include "internal.hpp"
@@ -98,6 +99,11 @@ const FourStepVariant& four_step_at(int i) {
 
 const FourStepVariant* find_four_step(const char* name) {
   if (!name) return nullptr;
+  // Names of tiled splits that differed in their first stage's exchange only,
+  // which the column kernels have one form of.
+  for (const auto& old : {std::make_pair("fs262144_tile512x512_c2", "fs262144_tile512x512"),
+                          std::make_pair("fs1048576_tile1024x1024_c2", "fs1048576_tile1024x1024")})
+    if (std::strcmp(old.first, name) == 0) name = old.second;
   for (int i = 0; i < num_four_step(); ++i)
     if (std::strcmp(four_step_at(i).name, name) == 0) return &four_step_at(i);
   return nullptr;
@@ -112,8 +118,8 @@ void build_stockham_twiddles(const SingleVariant& v, std::vector<float>& out) {
   stockham_twiddles(v.radix, v.npass, v.paired_twiddles, out);
 }
 
-// The four-step table, plus (tiled splits with N1 != N2) the second stage's
-// N1-point single-pass table appended.
+// The roots of a four-step split: the stage table, plus (column splits with
+// N1 != N2) the N1-point table appended.
 void build_four_step_twiddles(const FourStepVariant& f, std::vector<float>& out) {
   four_step_twiddles(f.n1, f.n2, f.two_level, out);
   if (f.two_level && f.sub2_name) {
@@ -240,26 +246,26 @@ const BuiltinEntry kBuiltin[] = {
     {16384, 769, 1536, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
     {16384, 1537, 4096, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
     {16384, 4097, INT64_MAX, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {32768, 1, 64, "fs32768_2x16384"},
-    {32768, 65, 384, "fs32768_2x16384"},
-    {32768, 385, 768, "fs32768_2x16384"},
-    {32768, 769, 1536, "fs32768_2x16384"},
-    {32768, 1537, 4096, "fs32768_2x16384"},
-    {32768, 4097, INT64_MAX, "fs32768_2x16384"},
+    {32768, 1, 64, "fs32768_tile128x256"},
+    {32768, 65, 384, "fs32768_tile128x256"},
+    {32768, 385, 768, "fs32768_tile128x256"},
+    {32768, 769, 1536, "fs32768_tile128x256"},
+    {32768, 1537, 4096, "fs32768_tile128x256"},
+    {32768, 4097, INT64_MAX, "fs32768_tile128x256"},
     {65536, 1, 64, "fs65536_tile256x256"},
-    {65536, 65, 384, "fs65536_4x16384"},
+    {65536, 65, 384, "fs65536_tile256x256"},
     {65536, 385, 768, "fs65536_tile256x256"},
-    {65536, 769, 1536, "fs65536_4x16384"},
-    {65536, 1537, 4096, "fs65536_4x16384"},
-    {65536, 4097, INT64_MAX, "fs65536_4x16384"},
+    {65536, 769, 1536, "fs65536_tile256x256"},
+    {65536, 1537, 4096, "fs65536_tile256x256"},
+    {65536, 4097, INT64_MAX, "fs65536_tile256x256"},
     {131072, 1, 64, "fs131072_tile256x512"},
     {131072, 65, 384, "fs131072_tile256x512"},
     {131072, 385, 768, "fs131072_tile256x512"},
-    {131072, 769, 1536, "fs131072_8x16384"},
-    {131072, 1537, 4096, "fs131072_8x16384"},
-    {131072, 4097, INT64_MAX, "fs131072_8x16384"},
-    {262144, 1, 64, "fs262144_tile512x512_c2"},
-    {262144, 65, 384, "fs262144_tile512x512_c2"},
+    {131072, 769, 1536, "fs131072_tile256x512"},
+    {131072, 1537, 4096, "fs131072_tile256x512"},
+    {131072, 4097, INT64_MAX, "fs131072_tile256x512"},
+    {262144, 1, 64, "fs262144_tile512x512"},
+    {262144, 65, 384, "fs262144_tile512x512"},
     {262144, 385, 768, "fs262144_tile512x512"},
     {262144, 769, 1536, "fs262144_tile512x512"},
     {262144, 1537, 4096, "fs262144_tile512x512"},
@@ -270,12 +276,12 @@ const BuiltinEntry kBuiltin[] = {
     {524288, 769, 1536, "fs524288_tile1024x512"},
     {524288, 1537, 4096, "fs524288_tile1024x512"},
     {524288, 4097, INT64_MAX, "fs524288_tile1024x512"},
-    {1048576, 1, 64, "fs1048576_tile1024x1024_c2"},
-    {1048576, 65, 384, "fs1048576_tile1024x1024_c2"},
-    {1048576, 385, 768, "fs1048576_tile1024x1024_c2"},
-    {1048576, 769, 1536, "fs1048576_tile1024x1024_c2"},
-    {1048576, 1537, 4096, "fs1048576_tile1024x1024_c2"},
-    {1048576, 4097, INT64_MAX, "fs1048576_tile1024x1024_c2"},
+    {1048576, 1, 64, "fs1048576_tile1024x1024"},
+    {1048576, 65, 384, "fs1048576_tile1024x1024"},
+    {1048576, 385, 768, "fs1048576_tile1024x1024"},
+    {1048576, 769, 1536, "fs1048576_tile1024x1024"},
+    {1048576, 1537, 4096, "fs1048576_tile1024x1024"},
+    {1048576, 4097, INT64_MAX, "fs1048576_tile1024x1024"},
 };
 
 // Built-in matched-filter choices: the autotuner's result on MI355X (the
@@ -792,8 +798,10 @@ extern "C" int fft_plan_config(fft_plan_t* plan, int64_t n, int64_t batch, int d
   p->algorithm = fs ? FFT_ALGO_FOUR_STEP : FFT_ALGO_SINGLE_PASS;
 
   std::vector<float> host;
-  build_stockham_twiddles(*sv, host);
-  rc = upload(host, &p->d_tw);
+  if (!fs || !fs->column()) {
+    build_stockham_twiddles(*sv, host);
+    rc = upload(host, &p->d_tw);
+  }
   if (!rc && !fs && direction == FFT_FORWARD) {
     // The kernels that run two transforms per load (matched filter, fused
     // forward -> weight -> adjoint): the named variant, else each kernel's
@@ -853,7 +861,10 @@ extern "C" int fft_plan_config(fft_plan_t* plan, int64_t n, int64_t batch, int d
     if (mv) p->tw_mma = same ? p->d_tw : p->d_tw_mma;
   }
   if (!rc && fs) {
-    build_four_step_twiddles(*fs, host);
+    if (fs->column())
+      column_twiddles(fs->column_shape, host);
+    else
+      build_four_step_twiddles(*fs, host);
     rc = upload(host, &p->d_tw4);
     if (!rc) {
       p->ws_bytes = (size_t)n * (size_t)batch * 8;
@@ -889,7 +900,7 @@ extern "C" int fft_exec(fft_plan_t plan, const void* in, void* out, void* stream
   const bool inv = plan->direction == FFT_BACKWARD;
   hipError_t e;
   if (plan->algorithm == FFT_ALGO_FOUR_STEP) {
-    e = plan->fs->columns(in, plan->d_ws, plan->d_tw, plan->batch, inv, s);
+    e = plan->fs->columns(in, plan->d_ws, plan->d_tw, plan->d_tw4, plan->batch, inv, s);
     if (e == hipSuccess) e = plan->fs->combine(plan->d_ws, out, plan->d_tw, plan->d_tw4, plan->batch, inv,
                                               s);
   } else {

@@ -21,6 +21,9 @@ constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kRsrcBytes = 0x7fffffff;
 // Cache policy of the access: 0 ordinary, kNT streamed once (nontemporal).
 constexpr int kNT = 2;
+// Store at device scope: written through the L2 at once instead of staying
+// there as a dirty line until the kernel ends.
+constexpr int kDeviceScope = 16;
 
 struct Buf {
   __amdgpu_buffer_rsrc_t r;

@@ -854,8 +854,8 @@ __global__ __launch_bounds__(256) void k_four_step_combine(const c32* y, c32* ou
 }
 
 template <class S, int N1>
-hipError_t launch_four_step_columns(const void* x, void* y, const void* tw, int64_t batch,
-                                    bool inverse, hipStream_t s) {
+hipError_t launch_four_step_columns(const void* x, void* y, const void* tw, const void* /*tw4*/,
+                                    int64_t batch, bool inverse, hipStream_t s) {
   // Rows are processed in chunks of kXcds * (max groups) so the block index fits.
   const int64_t units = max_groups_per_launch() / (kXcds * N1);
   const int64_t rows_per_launch = (units > 0 ? units : 1) * kXcds;

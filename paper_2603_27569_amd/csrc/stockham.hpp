@@ -66,13 +66,28 @@ constexpr float kC1 = 0.923879532511286756128f;  // cos(pi/8)
 constexpr float kS1 = 0.382683432365089771728f;  // sin(pi/8)
 constexpr float kR2 = 0.707106781186547524401f;  // cos(pi/4)
 
+// cos(k pi / 16), any k >= 0, by symmetry from the rounded first-quadrant values.
+constexpr float cos_pi16(int k) {
+  constexpr float q[9] = {1.0f, 0.980785280403230449126f, kC1, 0.831469612302545237079f, kR2,
+                          0.555570233019602224743f, kS1, 0.195090322016128267848f, 0.0f};
+  k &= 31;
+  if (k > 16) k = 32 - k;
+  return k <= 8 ? q[k] : -q[16 - k];
+}
+constexpr float sin_pi16(int k) { return cos_pi16(k + 24); }
+
 // v * W_R^k for the direction (W = e^{-2 pi i / R} forward, its conjugate
 // backward), with k and R compile-time; exact roots need no multiply.
 template <int R, int K, bool INV>
 __device__ __forceinline__ c32 mul_root(c32 v) {
   constexpr int k16 = (K * 16 / R) & 15;  // the same root expressed in W_16
-  static_assert((K * 16) % R == 0, "roots beyond W_16 are not tabulated");
-  if constexpr (k16 == 0) {
+  static_assert((K * 32) % R == 0, "roots beyond W_32 are not tabulated");
+  if constexpr ((K * 16) % R != 0) {  // odd multiples of pi/16
+    constexpr int k32 = K * 32 / R;
+    constexpr float c = cos_pi16(k32);
+    constexpr float s = INV ? sin_pi16(k32) : -sin_pi16(k32);
+    return {c * v.x - s * v.y, c * v.y + s * v.x};
+  } else if constexpr (k16 == 0) {
     return v;
   } else if constexpr (k16 == 4) {
     return mul_w4<INV>(v);
@@ -98,7 +113,7 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
 }
 
 // ---------------------------------------------------------------- DFT_R
-// In-register length-R DFT, R in {2, 4, 8, 16}, natural-order in and out,
+// In-register length-R DFT, R in {2, 4, 8, 16, 32}, natural-order in and out,
 // by radix-2 decimation in time: DFT_R = combine(DFT_{R/2}(even),
 // W_R^k * DFT_{R/2}(odd)).  For R = 8 this is the split DIT butterfly of
 // Section V-B, eq. (4).

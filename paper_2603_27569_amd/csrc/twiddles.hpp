@@ -89,4 +89,39 @@ inline void four_step_twiddles(int64_t n1, int64_t n2, bool two_level, std::vect
   for (int64_t j = 0; j < n1; ++j) put(j, n1);
 }
 
+// Tables of a column split N = N1 x N2 (columns.hpp) whose N2-point stage-1
+// columns run as R0 x R1 = c.r0_first x c.r1_first and whose N1-point stage-2
+// columns as c.r0_second x c.r1_second in tiles of KB = c.tile_second, one
+// after another, every entry rounded once:
+//   P1  [k][t] = W_N2^{k t}, k < R0, t < R1 of stage 1;
+//   P2  the same with W_N1 for stage 2;
+//   A   [tile][t][s] = W_N^{k2 t}, k2 = tile KB + s, t < R1 of stage 2;
+//   B   [tile][m][s] = W_{N / R1}^{k2 m}, m < R0 of stage 2,
+// so that W_N^{n1 k2} = A B for n1 = t + R1 m.
+struct ColumnShape {
+  int r0_first, r1_first, r0_second, r1_second, tile_second;
+};
+inline void column_twiddles(const ColumnShape& c, std::vector<float>& out) {
+  const int64_t n2 = (int64_t)c.r0_first * c.r1_first, n1 = (int64_t)c.r0_second * c.r1_second;
+  const int64_t N = n1 * n2;
+  out.clear();
+  auto put = [&](int64_t m, int64_t L) {
+    float re, im;
+    root_f32(m % L, L, &re, &im);
+    out.push_back(re);
+    out.push_back(im);
+  };
+  for (int k = 0; k < c.r0_first; ++k)
+    for (int t = 0; t < c.r1_first; ++t) put((int64_t)k * t, n2);
+  for (int k = 0; k < c.r0_second; ++k)
+    for (int t = 0; t < c.r1_second; ++t) put((int64_t)k * t, n1);
+  auto tiled = [&](int count, int64_t L) {
+    for (int64_t k0 = 0; k0 < n2; k0 += c.tile_second)
+      for (int i = 0; i < count; ++i)
+        for (int s = 0; s < c.tile_second; ++s) put((k0 + s) * i, L);
+  };
+  tiled(c.r1_second, N);
+  tiled(c.r0_second, N / c.r1_second);
+}
+
 }  // namespace stockfft

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "twiddles.hpp"
+
 namespace stockfft {
 
 constexpr int kMaxPasses = 8;
@@ -75,9 +77,10 @@ extern const int kNumSingleVariants;
 // the stage's own table).
 using FourStepCombineFn = hipError_t (*)(const void* y, void* out, const void* tw, const void* tw4,
                                          int64_t batch, bool inverse, hipStream_t s);
-// Four-step first stage: Y[b][n1][.] = FFT_N2(x[b][n1 + N1 m], m = 0..N2-1)
-using FourStepColumnsFn = hipError_t (*)(const void* x, void* y, const void* tw, int64_t batch,
-                                         bool inverse, hipStream_t s);
+// Four-step first stage: Y[b][n1][.] = FFT_N2(x[b][n1 + N1 m], m = 0..N2-1), in
+// the order the variant's second stage reads it.
+using FourStepColumnsFn = hipError_t (*)(const void* x, void* y, const void* tw, const void* tw4,
+                                         int64_t batch, bool inverse, hipStream_t s);
 
 struct FourStepVariant {
   const char* name;
@@ -91,9 +94,12 @@ struct FourStepVariant {
   // two short tables, lo[j] = W_N^j (j < 2^s) and hi[j] = W_N^{j 2^s}
   // (j < N / 2^s), s = floor(log2 N / 2), followed by W_N1^j (j < N1).
   bool two_level;
-  // Tiled splits with N1 != N2: the N1-point single-pass shape whose table
-  // the second stage runs on, appended to the stage table (else null).
-  const char* sub2_name;
+  // Column splits (columns.hpp; tile_second > 0): both stages run on
+  // column_twiddles' tables, passed as tw4 (tw is null).  two_level and the
+  // sub shapes then only describe the roots of the split.
+  const char* sub2_name;  // N1-point shape of splits with N1 != N2 (or null)
+  ColumnShape column_shape;
+  bool column() const { return column_shape.tile_second > 0; }
 };
 
 const FourStepVariant* four_step_variants(int* count);
