@@ -14,7 +14,8 @@ namespace stockfft {
 // Streaming (nontemporal) global accesses for the transform data: every input
 // element is read once and every output element written once, so the hint
 // keeps them from displacing the shared twiddle tables and lets the output
-// drain to memory while the kernel still runs instead of at its end.  The
+// drain to memory while the kernel still runs instead of at its end.  Loads
+// of rows that may still be in the Infinity Cache go without (stream_rows).  The
 // four-step's stride-N1 column loads keep ordinary accesses (their cache
 // lines are shared between workgroups; the hint there cost up to 1.5x at
 // N = 2^20), and so does its workspace, which the second stage reads back;
@@ -42,18 +43,14 @@ __device__ __forceinline__ int out_position(int t, int m) { return read_position
 // row that exists (its result is never stored), which costs nothing, where
 // zeroing its registers costs one instruction per register on every lane.
 template <class S>
-__device__ __forceinline__ void global_load_row(c32 (&a)[S::E], const c32* src, int t) {
-  if constexpr (paired_pass<S, 0>()) {
-    // slots m and m + 1 (m even) are adjacent elements: one 16-byte load
-#pragma unroll
-    for (int m = 0; m < S::E; m += 2) {
-      const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + in_position<S>(t, m)));
-      a[m] = c32{v.x, v.y};
-      a[m + 1] = c32{v.z, v.w};
-    }
-  } else {
+__device__ __forceinline__ void global_load_row(c32 (&a)[S::E], const c32* src, int t, int stream) {
+  static_assert(!paired_lanes<S>::value, "plain lane order");
+  if (stream) {  // uniform
 #pragma unroll
     for (int m = 0; m < S::E; ++m) a[m] = load_stream(src + t + m * S::T);
+  } else {
+#pragma unroll
+    for (int m = 0; m < S::E; ++m) a[m] = src[t + m * S::T];
   }
 }
 

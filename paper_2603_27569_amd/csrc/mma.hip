@@ -131,7 +131,7 @@ __device__ __forceinline__ V gather_halves(const uint32_t (&d)[8], bool hi) {
 // transforms in flight.  One wave per workgroup is held to two waves per SIMD.
 template <int N, int THREADS, int TPWG, bool INV, class IO>
 __global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma(
-    const uint32_t* in, uint32_t* out, const c32* tw, int64_t rows) {
+    const uint32_t* in, uint32_t* out, const c32* tw, int64_t rows, int stream) {
   using M = MmaPlan<N>;
   constexpr int NB = M::NB;
   constexpr int BPT = NB / 32;  // blocks per transform
@@ -181,9 +181,14 @@ __global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma
 #pragma unroll
   for (int b = 0; b < kBlocks; ++b) {
     const uint32_t* src = in + (row0 + tr[b]) * N;
+    if (stream) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      d[b][e] = live[b] ? __builtin_nontemporal_load(src + j[b] + (8 * h + e) * NB) : 0u;
+      for (int e = 0; e < 8; ++e)
+        d[b][e] = live[b] ? __builtin_nontemporal_load(src + j[b] + (8 * h + e) * NB) : 0u;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[b][e] = live[b] ? src[j[b] + (8 * h + e) * NB] : 0u;
+    }
   }
 
 #pragma unroll
@@ -279,6 +284,7 @@ template <int N, int THREADS, class IO, int TPWG = 1>
 hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t batch,
                               bool inverse, hipStream_t s) {
   const int64_t cap = max_groups_per_launch() * TPWG;  // rows per launch
+  const int stream = stream_rows(2 * batch * N * (int64_t)sizeof(uint32_t));
   for (int64_t r0 = 0; r0 < batch; r0 += cap) {
     const int64_t rows = batch - r0 < cap ? batch - r0 : cap;
     const uint32_t* ip = static_cast<const uint32_t*>(in) + r0 * N;
@@ -286,9 +292,9 @@ hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t
     const c32* twp = static_cast<const c32*>(tw);
     const dim3 grid((unsigned)((rows + TPWG - 1) / TPWG)), block(THREADS);
     if (inverse)
-      k_stockham_mma<N, THREADS, TPWG, true, IO><<<grid, block, 0, s>>>(ip, op, twp, rows);
+      k_stockham_mma<N, THREADS, TPWG, true, IO><<<grid, block, 0, s>>>(ip, op, twp, rows, stream);
     else
-      k_stockham_mma<N, THREADS, TPWG, false, IO><<<grid, block, 0, s>>>(ip, op, twp, rows);
+      k_stockham_mma<N, THREADS, TPWG, false, IO><<<grid, block, 0, s>>>(ip, op, twp, rows, stream);
   }
   return hipGetLastError();
 }

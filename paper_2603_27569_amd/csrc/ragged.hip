@@ -113,6 +113,7 @@ struct RaggedArgs {
   // Workgroup w runs tasks [r[0], r[7]) of the list, r = wg_cls + 8w; its
   // tasks of length 256 << c are [r[6 - c], r[7 - c]).
   const int* wg_cls;
+  int stream;               // cache policy of the row loads (stream_rows)
   int alt[kClasses];        // shape chosen for length 256 << c (0 = A, 1 = B)
   const c32* tw[kClasses];  // twiddle table of the chosen shape
 };
@@ -137,7 +138,7 @@ __device__ __forceinline__ void run_class_serial(int pos, int end, const RaggedA
     c32 a[S::E];
     // A dead slot (off = 0) reads the buffer's first N elements, which exist:
     // a length class has a task only if an item of that length does.
-    global_load_row<S>(a, A.in + off, t);
+    global_load_row<S>(a, A.in + off, t, A.stream);
     const bool more = pos + 1 < end;
     Task tn = tc;
     int64_t off_n = 0;
@@ -394,6 +395,7 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
   p->args.tasks = p->d_tasks;
   p->args.item_off = p->d_off;
   p->args.wg_cls = p->d_wg;
+  p->args.stream = stream_rows(2 * total * (int64_t)sizeof(c32));
 
   for (int c = 0; c < kClasses; ++c) p->args.tw[c] = static_cast<const c32*>(p->d_tw[c]);
   register_handle(p);
