@@ -360,8 +360,9 @@ int fft_set_launch_limit(int64_t max_groups);
  *   radices, lds_layout, exchange_rounds, barriers, twiddle_schedule, ...),
  *   whether it has the fused forward -> weight -> adjoint kernel
  *   ("fused_kernel") and also the matched filter ("fused_kernels"), its
- *   persistent workgroups per CU ("streamed", 0 for a workgroup per row)
- *   and, for the in-wave exchange shapes at N = 4096, the groups and
+ *   persistent workgroups per CU ("streamed", 0 for a workgroup per row),
+ *   whether its rows are loaded without the streaming hint
+ *   ("ordinary_loads") and, for the in-wave exchange shapes at N = 4096, the groups and
  *   members of a group per lane ("wave_exchange", "wave_members"; 0 for
  *   shapes that exchange through the LDS only).
  * fft_variant_twiddles: the FP32 twiddle table of variant `index` as built

@@ -204,131 +204,131 @@ struct BuiltinEntry {
   const char* name;
 };
 const BuiltinEntry kBuiltin[] = {
-    {256, 1, 64, "n256_e16_b4_p4_r16.16"},
-    {256, 65, 384, "n256_e16_b4_p4_r16.16_pt"},
-    {256, 385, 768, "n256_e8_b8_p4_r8.8.4"},
-    {256, 769, 1536, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 1537, 4096, "n256_e8_b8_p4_r8.8.4"},
-    {256, 4097, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt"},
-    {512, 1, 64, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 65, 384, "n512_e16_b2_p4_r16.16.2"},
-    {512, 385, 768, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 769, 1536, "n512_e16_b2_p4_r16.16.2_pt"},
-    {512, 1537, 4096, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt"},
-    {1024, 1, 64, "n1024_e8_b2_p4_r8.8.8.2"},
-    {1024, 65, 384, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {1024, 385, 768, "n1024_e16_b1_p4_r16.16.4"},
-    {1024, 769, 1536, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 1537, 4096, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {1024, 4097, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt"},
-    {2048, 1, 64, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 65, 384, "n2048_e8_b1_p4_r8.8.8.4"},
-    {2048, 385, 768, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 769, 1536, "n2048_e16_b1_p4_r16.16.8_pt"},
-    {2048, 1537, 4096, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
-    {2048, 4097, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
-    {4096, 1, 64, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
-    {4096, 65, 384, "n4096_e16_b1_px_r8.8.8.8_pt_wm2"},
-    {4096, 385, 768, "n4096_e8_b1_px_r8.8.8.8_pt"},
-    {4096, 769, 1536, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
-    {4096, 1537, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
-    {4096, 4097, INT64_MAX, "n4096_e8_b1_p4_r8.8.8.8_pt_tall_st1d3"},
-    {8192, 1, 64, "fs8192_4x2048"},
-    {8192, 65, 384, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
-    {8192, 385, 768, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
-    {8192, 769, 1536, "n8192_e32_c4_b1_p4_r8.8.8.16"},
-    {8192, 1537, 4096, "n8192_e32_c4_b1_p4_r8.8.8.16"},
-    {8192, 4097, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {16384, 1, 64, "fs16384_8x2048"},
-    {16384, 65, 384, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 385, 768, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {16384, 769, 1536, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {16384, 1537, 4096, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {16384, 4097, INT64_MAX, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {32768, 1, 64, "fs32768_tile128x256"},
-    {32768, 65, 384, "fs32768_tile128x256"},
-    {32768, 385, 768, "fs32768_tile128x256"},
-    {32768, 769, 1536, "fs32768_tile128x256"},
-    {32768, 1537, 4096, "fs32768_tile128x256"},
-    {32768, 4097, INT64_MAX, "fs32768_tile128x256"},
-    {65536, 1, 64, "fs65536_tile256x256"},
-    {65536, 65, 384, "fs65536_tile256x256"},
-    {65536, 385, 768, "fs65536_tile256x256"},
-    {65536, 769, 1536, "fs65536_tile256x256"},
-    {65536, 1537, 4096, "fs65536_tile256x256"},
-    {65536, 4097, INT64_MAX, "fs65536_tile256x256"},
-    {131072, 1, 64, "fs131072_tile256x512"},
-    {131072, 65, 384, "fs131072_tile256x512"},
-    {131072, 385, 768, "fs131072_tile256x512"},
-    {131072, 769, 1536, "fs131072_tile256x512"},
-    {131072, 1537, 4096, "fs131072_tile256x512"},
-    {131072, 4097, INT64_MAX, "fs131072_tile256x512"},
-    {262144, 1, 64, "fs262144_tile512x512"},
-    {262144, 65, 384, "fs262144_tile512x512"},
-    {262144, 385, 768, "fs262144_tile512x512"},
-    {262144, 769, 1536, "fs262144_tile512x512"},
-    {262144, 1537, 4096, "fs262144_tile512x512"},
-    {262144, 4097, INT64_MAX, "fs262144_tile512x512"},
-    {524288, 1, 64, "fs524288_tile1024x512"},
-    {524288, 65, 384, "fs524288_tile1024x512"},
-    {524288, 385, 768, "fs524288_tile1024x512"},
-    {524288, 769, 1536, "fs524288_tile1024x512"},
-    {524288, 1537, 4096, "fs524288_tile1024x512"},
-    {524288, 4097, INT64_MAX, "fs524288_tile1024x512"},
-    {1048576, 1, 64, "fs1048576_tile1024x1024"},
-    {1048576, 65, 384, "fs1048576_tile1024x1024"},
-    {1048576, 385, 768, "fs1048576_tile1024x1024"},
-    {1048576, 769, 1536, "fs1048576_tile1024x1024"},
-    {1048576, 1537, 4096, "fs1048576_tile1024x1024"},
-    {1048576, 4097, INT64_MAX, "fs1048576_tile1024x1024"},
+    {256, 1, 160, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 161, 256, "n256_e16_b4_p4_r16.16_pt_ol"},
+    {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 385, 512, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 513, 1024, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 1025, 2048, "n256_e16_b4_p4_r16.16"},
+    {256, 2049, 6144, "n256_e16_b4_p4_r16.16_pt"},
+    {256, 6145, 8192, "n256_e16_b4_p4_r16.16_pt_ol"},
+    {256, 8193, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {512, 1, 512, "n512_e4_b2_p4_r4.4.4.4.2"},
+    {512, 513, 1024, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 1025, 1536, "n512_e16_b2_p4_r16.16.2"},
+    {512, 1537, 2048, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 2049, 4096, "n512_e16_b2_p4_r16.16.2_pt"},
+    {512, 4097, 8192, "n512_e32_b4_p4_r32.16_pt"},
+    {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {1024, 1, 16, "n1024_e4_b1_p4_r4.4.4.4.4"},
+    {1024, 17, 64, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 65, 256, "n1024_e4_b1_p4_r4.4.4.4.4"},
+    {1024, 257, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 769, 1536, "n1024_e16_b1_p4_r16.16.4_pt"},
+    {1024, 1537, 2048, "n1024_e32_b2_p4_r32.32_pt"},
+    {1024, 2049, 3072, "n1024_e32_b4_p4_r32.32_pt"},
+    {1024, 3073, 4096, "n1024_e32_b2_p4_r32.32_pt"},
+    {1024, 4097, 6144, "n1024_e32_b2_p4_r32.32_pt_ol"},
+    {1024, 6145, 8192, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
+    {1024, 8193, INT64_MAX, "n1024_e32_b2_p4_r32.32_pt_ol"},
+    {2048, 1, 512, "n2048_e8_b1_p4_r8.8.8.4_pt"},
+    {2048, 513, 1024, "n2048_e16_b1_p4_r16.16.8_pt"},
+    {2048, 1025, 1536, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {2048, 1537, 3072, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
+    {2048, 3073, 6144, "n2048_e32_c2_b1_p4_r16.16.8_pt_ol"},
+    {2048, 6145, 8192, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
+    {2048, 8193, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
+    {4096, 1, 160, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
+    {4096, 161, 256, "n4096_e16_b1_px_r8.8.8.8_pt_wm2"},
+    {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt_tall"},
+    {4096, 385, 512, "n4096_e16_b1_p5_r16.16.16_pt"},
+    {4096, 513, 1024, "n4096_e32_b1_p4_r16.16.16_pt_pl"},
+    {4096, 1025, 1536, "n4096_e32_c2_b1_p4_r16.16.16_pt_pl"},
+    {4096, 1537, 2048, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
+    {4096, 2049, 3072, "n4096_e32_c2_b1_p4_r16.16.16_pt_ol"},
+    {4096, 3073, 4096, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
+    {4096, 4097, 8192, "n4096_e16_b1_p5_r16.16.16_pt"},
+    {4096, 8193, INT64_MAX, "n4096_e8_b1_p4_r8.8.8.8_pt_tall_st1d1"},
+    {8192, 1, 16, "fs8192_4x2048"},
+    {8192, 17, 160, "n8192_e16_b1_p4_r16.16.16.2_pt"},
+    {8192, 161, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
+    {8192, 513, 768, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {8192, 769, 1024, "n8192_e32_c4_b1_p4_r8.8.8.16"},
+    {8192, 1025, 1536, "n8192_e32_c2_b1_p4_r16.16.32_pt_ol"},
+    {8192, 1537, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {16384, 1, 16, "fs16384_8x2048"},
+    {16384, 17, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
+    {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
+    {16384, 257, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 513, 768, "n16384_e64_c2_b1_p4_r32.32.16_pt_ol"},
+    {16384, 769, 1024, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 1025, 3072, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 3073, 4096, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
+    {16384, 4097, 6144, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 6145, 8192, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 8193, INT64_MAX, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
+    {32768, 1, INT64_MAX, "fs32768_tile128x256"},
+    {65536, 1, INT64_MAX, "fs65536_tile256x256"},
+    {131072, 1, INT64_MAX, "fs131072_tile256x512"},
+    {262144, 1, INT64_MAX, "fs262144_tile512x512"},
+    {524288, 1, INT64_MAX, "fs524288_tile1024x512"},
+    {1048576, 1, INT64_MAX, "fs1048576_tile1024x1024"},
 };
 
 // Built-in matched-filter choices: the autotuner's result on MI355X (the
 // "filter_entries" of the package's tune_gfx950.json).
 const BuiltinEntry kBuiltinFilter[] = {
-    {256, 1, 64, "n256_e16_b4_p4_r16.16"},
-    {256, 65, 384, "n256_e16_b4_p4_r16.16_pt"},
-    {256, 385, 768, "n256_e16_b4_p4_r16.16_pt"},
-    {256, 769, 1536, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 1537, 4096, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 4097, INT64_MAX, "n256_e16_b4_p4_r16.16_pt"},
-    {512, 1, 64, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 65, 384, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 385, 768, "n512_e4_b2_p4_r4.4.4.4.2"},
-    {512, 769, 1536, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 1537, 4096, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt"},
-    {1024, 1, 64, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 65, 384, "n1024_e4_b1_p4_r4.4.4.4.4"},
-    {1024, 385, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 769, 1536, "n1024_e8_b2_p4_r8.8.8.2_pt"},
-    {1024, 1537, 4096, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {1024, 4097, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt"},
-    {2048, 1, 64, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 65, 384, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 385, 768, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 769, 1536, "n2048_e16_b1_p4_r16.16.8_pt"},
-    {2048, 1537, 4096, "n2048_e16_b1_p4_r16.16.8_pt"},
-    {2048, 4097, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
-    {4096, 1, 64, "n4096_e8_b1_p4_r8.8.8.8_pt"},
-    {4096, 65, 384, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {256, 1, 160, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 161, 256, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 385, 1024, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 1025, 2048, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 2049, 3072, "n256_e16_b4_p4_r16.16_pt"},
+    {256, 3073, 4096, "n256_e16_b4_p4_r16.16"},
+    {256, 4097, 8192, "n256_e16_b4_p4_r16.16_pt"},
+    {256, 8193, INT64_MAX, "n256_e16_b4_p4_r16.16_pt_ol"},
+    {512, 1, 512, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
+    {512, 513, 1024, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 1025, 1536, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
+    {512, 1537, 2048, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 2049, 4096, "n512_e16_b2_p4_r16.16.2_pt"},
+    {512, 4097, 8192, "n512_e32_b4_p4_r32.16_pt"},
+    {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {1024, 1, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 769, 2048, "n1024_e16_b1_p4_r16.16.4_pt"},
+    {1024, 2049, 3072, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 3073, 4096, "n1024_e32_b2_p4_r32.32_pt"},
+    {1024, 4097, 6144, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 6145, INT64_MAX, "n1024_e32_b2_p4_r32.32_pt_ol"},
+    {2048, 1, 512, "n2048_e8_b1_p4_r8.8.8.4_pt"},
+    {2048, 513, 1536, "n2048_e16_b1_p4_r16.16.8_pt"},
+    {2048, 1537, 3072, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {2048, 3073, 4096, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
+    {2048, 4097, 6144, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {2048, 6145, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
+    {4096, 1, 16, "n4096_e8_b1_p4_r8.8.8.8_pt_ol"},
+    {4096, 17, 256, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt_tall"},
     {4096, 385, 768, "n4096_e16_b1_p5_r16.16.16_pt"},
-    {4096, 769, 1536, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
-    {4096, 1537, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt_pl"},
+    {4096, 769, 1024, "n4096_e32_b1_p4_r16.16.16_pt_pl"},
+    {4096, 1025, 3072, "n4096_e32_c2_b1_p4_r16.16.16_pt_ol"},
+    {4096, 3073, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
     {4096, 4097, INT64_MAX, "n4096_e32_b1_p4_r16.16.16_pt_pl"},
     {8192, 1, 64, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 65, 384, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
-    {8192, 385, 768, "n8192_e32_b1_p4_r16.16.16.2_pt"},
-    {8192, 769, 1536, "n8192_e32_c4_b1_p4_r8.8.8.16"},
-    {8192, 1537, 4096, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {8192, 4097, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {16384, 1, 64, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 65, 384, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 385, 768, "n16384_e16_c2_b1_p4_r8.8.8.8.4_pt"},
-    {16384, 769, 1536, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 1537, 4096, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 4097, INT64_MAX, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {8192, 65, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
+    {8192, 513, 1536, "n8192_e32_c2_b1_p4_r16.16.32_pt_ol"},
+    {8192, 1537, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {16384, 1, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
+    {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
+    {16384, 257, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 513, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 769, 1024, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 1025, 2048, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 2049, 4096, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 4097, INT64_MAX, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
 };
 
 // Built-in 16-bit storage choices: the autotuner's result on MI355X (the
@@ -336,95 +336,101 @@ const BuiltinEntry kBuiltinFilter[] = {
 // move, so the balance between memory and arithmetic, and with it the best
 // shape, differs from the FP32 transform's.
 const BuiltinEntry kBuiltinStorage16[] = {
-    {256, 1, 64, "n256_e16_b4_p4_r16.16"},
-    {256, 65, 384, "n256_e8_b8_p4_r8.8.4"},
-    {256, 385, 768, "n256_e16_b4_p4_r16.16"},
-    {256, 769, 1536, "n256_e16_b4_p4_r16.16_pt"},
-    {256, 1537, 4096, "n256_e8_b8_p4_r8.8.4_pt"},
-    {256, 4097, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt"},
-    {512, 1, 64, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 65, 384, "n512_e16_b2_p4_r16.16.2"},
-    {512, 385, 768, "n512_e16_b2_p4_r16.16.2"},
-    {512, 769, 1536, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 1537, 4096, "n512_e8_b4_p4_r8.8.8"},
-    {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt"},
-    {1024, 1, 64, "n1024_e8_b2_p4_r8.8.8.2_pt"},
-    {1024, 65, 384, "n1024_e16_b4_p4_r16.16.4"},
-    {1024, 385, 768, "n1024_e8_b2_p4_r8.8.8.2"},
-    {1024, 769, 1536, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {1024, 1537, 4096, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {1024, 4097, INT64_MAX, "n1024_e16_b1_p4_r16.16.4_pt"},
-    {2048, 1, 64, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 65, 384, "n2048_e16_b1_p4_r16.16.8"},
-    {2048, 385, 768, "n2048_e8_b1_p4_r8.8.8.4"},
-    {2048, 769, 1536, "n2048_e16_b1_p4_r16.16.8_pt"},
-    {2048, 1537, 4096, "n2048_e16_b2_p4_r16.16.8_pt"},
-    {2048, 4097, INT64_MAX, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
-    {4096, 1, 64, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
-    {4096, 65, 384, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
-    {4096, 385, 768, "n4096_e8_b1_px_r8.8.8.8_pt"},
-    {4096, 769, 1536, "n4096_e32_b1_p4_r16.16.16_pt"},
-    {4096, 1537, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt_pl"},
+    {256, 1, 256, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 385, 2048, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 2049, 4096, "n256_e16_b4_p4_r16.16"},
+    {256, 4097, 8192, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {256, 8193, INT64_MAX, "n256_e16_b4_p4_r16.16_pt_ol"},
+    {512, 1, 384, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 385, 512, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
+    {512, 513, 4096, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 4097, 6144, "n512_e16_b2_p4_r16.16.2_pt"},
+    {512, 6145, 8192, "n512_e16_b2_p4_r16.16.2_pt_ol"},
+    {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {1024, 1, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 769, 1024, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
+    {1024, 1025, 2048, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 2049, 3072, "n1024_e16_b1_p4_r16.16.4_pt"},
+    {1024, 3073, 4096, "n1024_e32_b2_p4_r32.32_pt"},
+    {1024, 4097, INT64_MAX, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {2048, 1, 768, "n2048_e8_b1_p4_r8.8.8.4_pt"},
+    {2048, 769, 2048, "n2048_e16_b1_p4_r16.16.8_pt"},
+    {2048, 2049, 4096, "n2048_e32_c2_b1_p4_r16.16.8_pt"},
+    {2048, 4097, 6144, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {2048, 6145, 8192, "n2048_e32_c2_b1_p4_r16.16.8_pt_ol"},
+    {2048, 8193, INT64_MAX, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {4096, 1, 16, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {4096, 17, 64, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
+    {4096, 65, 256, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {4096, 257, 512, "n4096_e16_b1_px_r16.16.16_db_pt"},
+    {4096, 513, 768, "n4096_e16_b1_p5_r16.16.16_pt"},
+    {4096, 769, 1024, "n4096_e32_b1_p4_r16.16.16_pt"},
+    {4096, 1025, 1536, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
+    {4096, 1537, 2048, "n4096_e32_c2_b1_p4_r16.16.16_pt_pl"},
+    {4096, 2049, 4096, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
     {4096, 4097, INT64_MAX, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d2"},
-    {8192, 1, 64, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 65, 384, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 385, 768, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 769, 1536, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {8192, 1537, 4096, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 4097, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {16384, 1, 64, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 65, 384, "n16384_e32_b1_p4_r16.16.16.4_pt"},
-    {16384, 385, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 769, 1536, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 1537, 4096, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 4097, INT64_MAX, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {8192, 1, 160, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 161, 256, "n8192_e16_b1_p4_r16.16.16.2_pt"},
+    {8192, 257, 1024, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {8192, 1025, 3072, "n8192_e32_c2_b1_p4_r16.16.32_pt_ol"},
+    {8192, 3073, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {16384, 1, 16, "n16384_e16_b1_p4_r16.16.16.4_pt"},
+    {16384, 17, 256, "n16384_e32_b1_p4_r32.32.16_pt"},
+    {16384, 257, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 513, 2048, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 2049, INT64_MAX, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
 };
 
 // Built-in fused forward -> weight -> adjoint choices: the autotuner's result
 // on MI355X (the "fused_entries" of the package's tune_gfx950.json).
 const BuiltinEntry kBuiltinFused[] = {
-    {256, 1, 64, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 65, 384, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 385, 768, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 769, 1536, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 1537, 4096, "n256_e8_b8_p4_r8.8.4_pt"},
-    {256, 4097, INT64_MAX, "n256_e16_b16_p4_r16.16_pt"},
-    {512, 1, 64, "n512_e8_b4_p4_r8.8.8"},
-    {512, 65, 384, "n512_e4_b2_p4_r4.4.4.4.2"},
-    {512, 385, 768, "n512_e8_b4_p4_r8.8.8"},
-    {512, 769, 1536, "n512_e8_b4_p4_r8.8.8"},
-    {512, 1537, 4096, "n512_e8_b4_p4_r8.8.8_pt"},
-    {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt"},
+    {256, 1, 160, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 161, 256, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 385, 512, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 513, 1024, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 1025, 6144, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {256, 6145, 8192, "n256_e16_b16_p4_r16.16_pt"},
+    {256, 8193, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {512, 1, 160, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 161, 384, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
+    {512, 385, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {1024, 1, 64, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 65, 384, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 385, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 769, 1536, "n1024_e8_b2_p4_r8.8.8.2_pt"},
-    {1024, 1537, 4096, "n1024_e8_b2_p4_r8.8.8.2_pt"},
-    {1024, 4097, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt"},
-    {2048, 1, 64, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 65, 384, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 385, 768, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 769, 1536, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 1537, 4096, "n2048_e16_b2_p4_r16.16.8_pt"},
+    {1024, 65, 160, "n1024_e4_b1_p4_r4.4.4.4.4"},
+    {1024, 161, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 769, 2048, "n1024_e8_b2_p4_r8.8.8.2_pt"},
+    {1024, 2049, 3072, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
+    {1024, 3073, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
+    {2048, 1, 1024, "n2048_e8_b1_p4_r8.8.8.4_pt"},
+    {2048, 1025, 2048, "n2048_e16_b2_p4_r16.16.8_pt"},
+    {2048, 2049, 4096, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
     {2048, 4097, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
-    {4096, 1, 64, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
-    {4096, 65, 384, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
-    {4096, 385, 768, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
-    {4096, 769, 1536, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
-    {4096, 1537, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
-    {4096, 4097, INT64_MAX, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
-    {8192, 1, 64, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
-    {8192, 65, 384, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
-    {8192, 385, 768, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 769, 1536, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {8192, 1537, 4096, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {8192, 4097, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {16384, 1, 64, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 65, 384, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 385, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 769, 1536, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 1537, 4096, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 4097, INT64_MAX, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {4096, 1, 256, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
+    {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt_tall"},
+    {4096, 385, 512, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
+    {4096, 513, 768, "n4096_e16_b1_p5_r16.16.16_pt"},
+    {4096, 769, 1024, "n4096_e16_b1_px_r16.16.16_pt"},
+    {4096, 1025, 1536, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
+    {4096, 1537, 2048, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
+    {4096, 2049, INT64_MAX, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
+    {8192, 1, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
+    {8192, 513, 1024, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {8192, 1025, 1536, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
+    {8192, 1537, 8192, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {8192, 8193, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
+    {16384, 1, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
+    {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
+    {16384, 257, 512, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 513, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 769, 1024, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 1025, 1536, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 1537, 2048, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 2049, 3072, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
+    {16384, 3073, 8192, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 8193, INT64_MAX, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
 };
 
 // Single-pass fallback when a four-step choice is not wanted.
@@ -1168,7 +1174,7 @@ static std::string radices_json(const SingleVariant& v) {
 }
 
 static std::string describe_single(const SingleVariant& v) {
-  char buf[512];
+  char buf[640];
   std::snprintf(buf, sizeof buf,
                 "{\"kind\":\"single\",\"name\":\"%s\",\"n\":%d,\"values_per_lane\":%d,"
                 "\"lanes_per_transform\":%d,\"transforms_per_workgroup\":%d,\"pad_log2\":%d,"
@@ -1176,12 +1182,14 @@ static std::string describe_single(const SingleVariant& v) {
                 "\"passes\":%d,\"radices\":%s,\"exchange_rounds\":%d,\"threads\":%d,"
                 "\"lds_bytes\":%d,\"twiddle_entries\":%d,\"barriers\":%d,"
                 "\"double_buffered\":%s,\"twiddle_schedule\":%d,\"paired_twiddles\":%s,\"paired_lanes\":%s,"
+                "\"ordinary_loads\":%s,"
                 "\"fused_kernels\":%s,\"fused_kernel\":%s,\"streamed\":%d,\"wave_exchange\":%d,\"wave_members\":%d}",
                 v.name, v.n, v.e, v.t, v.tpb, v.padlog,
                 v.padlog > 0 ? "pad" : v.padlog < 0 ? "xor" : "none", v.npass, radices_json(v).c_str(),
                 v.chunks, v.threads, v.lds_bytes, v.tw_elems, barriers_of(v),
                 v.double_buffered ? "true" : "false", v.twiddle_schedule,
                 v.paired_twiddles ? "true" : "false", v.paired_lanes ? "true" : "false",
+                v.ordinary_loads ? "true" : "false",
                 v.fused && v.filter ? "true" : "false", v.fused ? "true" : "false", v.streamed,
                 v.wave_exchange, v.wave_members);
   return buf;

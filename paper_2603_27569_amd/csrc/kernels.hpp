@@ -64,14 +64,14 @@ __device__ __forceinline__ void buffer_load_row(c32 (&a)[S::E], const Buf& b, in
   if constexpr (paired_pass<S, 0>()) {
 #pragma unroll
     for (int m = 0; m < S::E; m += 2) {
-      const u32x4 v = b.ld128<kNT>(voff, 8 * in_position<S>(0, m));
+      const u32x4 v = b.ld128<row_policy<S>()>(voff, 8 * in_position<S>(0, m));
       a[m] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
       a[m + 1] = c32{__uint_as_float(v.z), __uint_as_float(v.w)};
     }
   } else {
 #pragma unroll
     for (int m = 0; m < S::E; ++m) {
-      const u32x2 v = b.ld64<kNT>(voff, 8 * in_position<S>(0, m));
+      const u32x2 v = b.ld64<row_policy<S>()>(voff, 8 * in_position<S>(0, m));
       a[m] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
     }
   }
@@ -226,13 +226,13 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham_io(const uint32
       // slots m and m + 1 (m even) are adjacent values: one 8-byte load
 #pragma unroll
       for (int m = 0; m < S::E; m += 2) {
-        const u32x2 v = src.ld64<kNT>(voff, 4 * in_position<S>(0, m));
+        const u32x2 v = src.ld64<row_policy<S>()>(voff, 4 * in_position<S>(0, m));
         a[m] = IO::load(v.x);
         a[m + 1] = IO::load(v.y);
       }
     } else {
 #pragma unroll
-      for (int m = 0; m < S::E; ++m) a[m] = IO::load(src.ld32<kNT>(voff, 4 * in_position<S>(0, m)));
+      for (int m = 0; m < S::E; ++m) a[m] = IO::load(src.ld32<row_policy<S>()>(voff, 4 * in_position<S>(0, m)));
     }
   }
   run_passes<S, INV>(a, lds, tw, t);

@@ -350,6 +350,27 @@ constexpr bool paired_pass() {
   else return (p == 0 || p == S::P - 1) && S::E / S::radix(p) >= 2;
 }
 
+// Ordinary row loads (_ol): the rows are loaded without the streaming hint,
+// which is 5 to 25% faster at small lengths and many rows while the rows are
+// in the 256 MiB Infinity Cache and 1 to 5% slower when they come from HBM
+// (512 x 4096: 7.8 -> 6.4 us against 8.2 -> 8.4; matched filter 1024 x 4000:
+// 19.3 -> 14.9 against 19.0 -> 19.5).  A property of the shape, so that the
+// tuner, which times both situations, decides; the policy as an argument of
+// the kernel cost 3 to 7% in the register-bound shapes (16384 x 1024: 53.1 ->
+// 56.9 us).
+template <class Base>
+struct OrdinaryLoads : Base {
+  static constexpr int ROW_POLICY = 0;
+};
+template <class S, class = void>
+struct row_policy_of : std::integral_constant<int, kNT> {};
+template <class S>
+struct row_policy_of<S, std::void_t<decltype(S::ROW_POLICY)>> : std::integral_constant<int, S::ROW_POLICY> {};
+template <class S>
+constexpr int row_policy() {
+  return row_policy_of<S>::value;
+}
+
 // Butterfly index of a lane's b-th butterfly in pass p.
 template <class S, int p>
 __device__ __forceinline__ int bfly_index(int t, int b) {

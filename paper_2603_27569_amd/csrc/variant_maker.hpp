@@ -22,6 +22,7 @@ SingleVariant make_variant(const char* name) {
   v.twiddle_schedule = S::PF;
   v.paired_twiddles = paired_twiddles<S>::value;
   v.paired_lanes = paired_lanes<S>::value;
+  v.ordinary_loads = row_policy<S>() != kNT;
   v.streamed = streamed<S>::value;
   v.threads = S::THREADS;
   v.lds_bytes = S::TPB * S::LDS_ELEMS * (int)sizeof(c32);

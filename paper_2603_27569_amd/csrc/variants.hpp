@@ -64,6 +64,7 @@ struct SingleVariant {
   int twiddle_schedule;  // 0 at their pass, 1 one pass ahead, 2 all with the input
   bool paired_twiddles;  // table layout: two twiddles per 16-byte entry (PairedTwiddles)
   bool paired_lanes;     // first/last pass in the paired butterfly order (PairedLanes)
+  bool ordinary_loads;   // rows loaded without the streaming hint (OrdinaryLoads)
   int streamed;          // 0: a workgroup per transform; k: k persistent workgroups per CU (Streamed)
   int wave_exchange;     // 0: every exchange through the LDS; G: in-wave exchanges, G groups per lane (WaveExchange)
   int wave_members;      // with in-wave exchanges: members of each group per lane (1 or 2)

@@ -4,6 +4,7 @@
 #include "variant_maker.hpp"
 
 using stockfft::DoubleBuffered;
+using stockfft::OrdinaryLoads;
 using stockfft::PairedLanes;
 using stockfft::PairedTwiddles;
 using stockfft::Shape;
@@ -68,6 +69,10 @@ STOCKFFT_VARIANT_GROUP(variants_4096,
       "n4096_e16_b1_px_r16.16.16_db_pt_tall_st1d1"),
   make_variant<Streamed<PairedTwiddles<ShapeX<1, 2, 1, 4096, 8, 1, 4, 8, 8, 8, 8>>, 1, 1>>(
       "n4096_e8_b1_p4_r8.8.8.8_pt_tall_st1d1"),
+  // Ordinary row loads.
+  make_variant<OrdinaryLoads<PairedTwiddles<ShapeX<2, false, 4, 4096, 32, 1, 4, 16, 16, 16>>>>(
+      "n4096_e32_c2_b1_p4_r16.16.16_pt_ol"),
+  make_variant<OrdinaryLoads<PairedTwiddles<Shape<4096, 8, 1, 4, 8, 8, 8, 8>>>>("n4096_e8_b1_p4_r8.8.8.8_pt_ol"),
   // In-wave exchanges after passes 0 and 2 (8 x 8 transposes by cross-lane
   // moves), the LDS only between passes 1 and 2: one barrier per transform.
   // _wx1: one group per lane (8-byte accesses in 64-byte runs); _wx2: two

@@ -22,13 +22,16 @@ Each plain entry also records, per single-pass candidate, the registers,
 scratch and LDS of its compiled kernel as the runtime reports them
 ("resources"), so a choice can be read against its occupancy and spills.
 
-Timing: back-to-back launches over a ring of independent buffers larger
-than the Infinity Cache, bracketed by HIP events on the launch stream; the
-median of three repeats, each at least REPEAT_US of GPU time; candidates
-within 3% of the best are timed again with three times the launches before
-one is chosen.  Every variant computes the same transform (the
-parity tests check each one against the FP64 reference), so the search is
-on speed alone.
+Timing: back-to-back launches captured into a HIP graph (so the host's launch
+rate is no limit), bracketed by HIP events; the median of three repeats, each
+at least REPEAT_US of GPU time; candidates within 3% of the best are timed
+again with three times the launches before one is chosen.  Each candidate is
+timed at two batches of the bucket and there twice, over a ring of independent
+buffers larger than the Infinity
+Cache (rows come from HBM) and over three inputs and two outputs (rows just
+produced, as far as they fit the cache), and scored by the geometric mean
+("us").  Every variant computes the same transform (the parity tests check
+each one against the FP64 reference), so the search is on speed alone.
 
 Usage: python -m paper_2603_27569_amd.tune [--out tune_gfx950.json] [--quick]
        python -m paper_2603_27569_amd.tune --run-variants N BATCH [--iters K]
@@ -54,9 +57,15 @@ SIZES = (256, 512, 1024, 2048, 4096, 8192, 16384)
 # Lengths with four-step splits only (plain transform; the fused kernels are
 # single-pass); the timed batch is capped by MAX_BYTES per buffer.
 SIZES_LARGE = tuple(1 << e for e in range(15, 21))
-# Batch buckets: (batch_min, batch_max, representative batch timed).
-BUCKETS = ((1, 64, 32), (65, 384, 256), (385, 768, 512), (769, 1536, 1024), (1537, 4096, 2048),
-           (4097, 2 ** 62, 16384))
+# Batch buckets: (batch_min, batch_max, representative batches timed): the
+# power of two a bucket ends at and a batch that is no multiple of the CU
+# count, so that no choice rests on a last round of workgroups that happens to
+# be full.
+BUCKETS = ((1, 16, (3, 8)), (17, 64, (24, 64)), (65, 160, (90, 128)), (161, 256, (200, 256)),
+           (257, 384, (290, 370)), (385, 512, (430, 512)), (513, 768, (560, 720)), (769, 1024, (850, 1024)),
+           (1025, 1536, (1100, 1450)), (1537, 2048, (1700, 2048)), (2049, 3072, (2300, 2900)),
+           (3073, 4096, (3500, 4096)), (4097, 6144, (4700, 5900)), (6145, 8192, (7000, 8192)),
+           (8193, 2 ** 62, (10000, 16384)))
 # Each timed repeat covers at least this much GPU time (launch counts adapt to
 # the kernel's duration), and the candidates within CLOSE of the best are
 # timed once more with FINAL_FACTOR times the launches before one is chosen.
@@ -64,58 +73,111 @@ REPEAT_US = 1500.0
 CLOSE = 1.03
 FINAL_FACTOR = 3
 RING_BYTES = 1 << 30
+RING_MAX = 400  # buffer pairs: below 640 KiB a pair is reused while still cached
 MAX_BYTES = 2 << 30  # cap on one timed buffer
 
 
+def _ring_size(buffer_bytes):
+    return min(RING_MAX, max(3, math.ceil(RING_BYTES / (2 * buffer_bytes))))
+
+
 def _ring(torch, dev, n, batch):
-    per = n * batch * 8
-    k = max(2, math.ceil(RING_BYTES / (2 * per)))
-    xs = [torch.randn(batch, n, dtype=torch.complex64, device=dev) for _ in range(k)]
-    ys = [torch.empty_like(xs[0]) for _ in range(k)]
+    k = _ring_size(n * batch * 8)
+    xs = list(torch.randn(k, batch, n, dtype=torch.complex64, device=dev))
+    ys = list(torch.empty(k, batch, n, dtype=torch.complex64, device=dev))
     return xs, ys
 
 
 def _time(torch, stream, fn, iters, warmup=5, repeats=3):
     """Median over `repeats` of the per-launch time of back-to-back launches
-    (microseconds).  `iters` is the least number of launches per repeat; it
-    grows so that a repeat covers REPEAT_US of GPU time."""
+    (microseconds): a graph of at least `iters` launches, replayed so that a
+    repeat covers REPEAT_US of GPU time."""
+    per = max(15, iters)
     with torch.cuda.stream(stream):
         for i in range(warmup):
             fn(i)
     torch.cuda.synchronize()
-    e0 = torch.cuda.Event(enable_timing=True)
-    e1 = torch.cuda.Event(enable_timing=True)
-    with torch.cuda.stream(stream):
-        e0.record(stream)
-        for i in range(5):
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for i in range(per):
             fn(i)
-        e1.record(stream)
-    torch.cuda.synchronize()
-    probe = max(e0.elapsed_time(e1) * 1e3 / 5, 1.0)
-    iters = max(iters, min(2000, int(REPEAT_US / probe)))
-    res = []
-    for _ in range(repeats):
+
+    def run(times):
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         with torch.cuda.stream(stream):
             e0.record(stream)
-            for i in range(iters):
-                fn(i)
+            for _ in range(times):
+                graph.replay()
             e1.record(stream)
         torch.cuda.synchronize()
-        res.append(e0.elapsed_time(e1) * 1e3 / iters)
-    return statistics.median(res)
+        return e0.elapsed_time(e1) * 1e3 / (times * per)
+
+    run(1)
+    probe = max(run(1), 0.5)
+    times = max(1, min(2000, int(REPEAT_US / probe)) // per)
+    return statistics.median(run(times) for _ in range(repeats))
 
 
-def _pick(times, retime):
-    """The fastest candidate, after re-timing every candidate within CLOSE of
-    the first measurement's best (retime(name) returns a new time)."""
-    best = min(times.values())
-    close = [k for k, v in times.items() if v <= best * CLOSE]
-    if len(close) > 1:
-        for k in close:
-            times[k] = retime(k)
-    return min(times, key=times.get)
+def _time_both(torch, stream, call, xs, ys, iters):
+    """Geometric mean of the per-launch times with rows from HBM (the whole
+    ring) and with rows just produced (three inputs, two outputs).
+    call(x, y) launches once."""
+    k = len(xs)
+    cold = _time(torch, stream, lambda i: call(xs[i % k], ys[i % k]), k)
+    m, o = min(3, k), min(2, k)
+    warm = _time(torch, stream, lambda i: call(xs[i % m], ys[i % o]), iters // 2)
+    return math.sqrt(cold * warm)
+
+
+def _batches(representative, buffer_bytes):
+    """The batches timed for a bucket: its representatives, halved until a
+    buffer of that many rows (buffer_bytes(batch)) fits MAX_BYTES."""
+    out = []
+    for b in representative if isinstance(representative, tuple) else (representative,):
+        while buffer_bytes(b) > MAX_BYTES and b > 1:
+            b //= 2
+        if b not in out:
+            out.append(b)
+    return out
+
+
+def _tune_table(torch, stream, sizes, buckets, iters, log, label, value_bytes, ring, names, plan, launch):
+    """One tuned table.  Per length n and bucket, every name of names(n) is
+    timed at the bucket's representative batches and scored by the geometric
+    mean of its times; those within CLOSE of a batch's best are timed again
+    there.  ring(n, batch) gives the buffers, plan(n, batch, name) a plan,
+    launch(n, batch) a function (plan, x, y) that launches once."""
+    entries = []
+    for n in sizes:
+        for bmin, bmax, representative in buckets:
+            batches = _batches(representative, lambda b: n * b * value_bytes)
+            logs = {}
+            for b in batches:
+                xs, ys = ring(n, b)
+                run = launch(n, b)
+
+                def timed(name, factor=1):
+                    p = plan(n, b, name)
+                    t = _time_both(torch, stream, lambda x, y: run(p, x, y), xs, ys, iters * factor)
+                    p.close()
+                    return t
+
+                times = {name: timed(name) for name in names(n)}
+                limit = min(times.values()) * CLOSE
+                close = [k for k, v in times.items() if v <= limit]
+                if len(close) > 1:
+                    times.update({k: timed(k, FINAL_FACTOR) for k in close})
+                for k, v in times.items():
+                    logs[k] = logs.get(k, 0.0) + math.log(v) / len(batches)
+                del xs, ys
+            score = {k: round(math.exp(v), 3) for k, v in logs.items()}
+            best = min(score, key=score.get)
+            log(f"tune {label} n={n} batch={batches} -> {best} {score[best]:.2f} us")
+            entries.append({"n": n, "batch_min": bmin, "batch_max": bmax, "variant": best,
+                            "timed_batch": batches[-1], "timed_batches": batches, "us": score[best],
+                            "candidates": score})
+    return entries
 
 
 def filter_candidates(n):
@@ -142,113 +204,55 @@ def candidates(n):
 
 
 def tune_plain(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=print):
-    entries = []
-    for n in sizes:
-        for bmin, bmax, b in buckets:
-            while n * b * 8 > MAX_BYTES and b > 1:
-                b //= 2
-            xs, ys = _ring(torch, dev, n, b)
-            k = len(xs)
-            times = {}
-            res = {}
-            cs = stream.cuda_stream
-            algos = dict(candidates(n))
+    cs = stream.cuda_stream
+    resources = {}
 
-            def timed(name, factor=1):
-                p = Plan(n, b, FFT_FORWARD, algos[name], name)
-                if algos[name] == FFT_ALGO_SINGLE_PASS and name not in res:
-                    r = p.describe().get("variant_resources")
-                    if r:
-                        res[name] = r
-                t = _time(torch, stream,
-                          lambda i: p.exec(xs[i % k].data_ptr(), ys[i % k].data_ptr(), cs),
-                          iters * factor)
-                p.close()
-                return t
+    def plan(n, b, name):
+        algo = dict(candidates(n))[name]
+        p = Plan(n, b, FFT_FORWARD, algo, name)
+        if algo == FFT_ALGO_SINGLE_PASS and name not in resources:
+            resources[name] = p.describe().get("variant_resources")
+        return p
 
-            for name in algos:
-                times[name] = timed(name)
-            best = _pick(times, lambda name: timed(name, FINAL_FACTOR))
-            log(f"tune n={n} batch={b} -> {best} {times[best]:.2f} us")
-            entries.append({"n": n, "batch_min": bmin, "batch_max": bmax, "variant": best,
-                            "timed_batch": b, "us": round(times[best], 3),
-                            "candidates": {k2: round(v, 3) for k2, v in times.items()},
-                            "resources": res})
-            del xs, ys
+    entries = _tune_table(torch, stream, sizes, buckets, iters, log, "plain", 8,
+                          lambda n, b: _ring(torch, dev, n, b), lambda n: list(dict(candidates(n))), plan,
+                          lambda n, b: lambda p, x, y: p.exec(x.data_ptr(), y.data_ptr(), cs))
+    for e in entries:
+        e["resources"] = {k: resources[k] for k in e["candidates"] if resources.get(k)}
     return entries
+
+
+def _single_plan(n, b, name):
+    return Plan(n, b, FFT_FORWARD, FFT_ALGO_SINGLE_PASS, name)
 
 
 def tune_filter(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=print):
     """The fused matched filter (forward, multiply by conj(h), inverse in one
     kernel) per length and batch bucket, over the single-pass variants."""
-    entries = []
-    for n in sizes:
+    cs = stream.cuda_stream
+
+    def launch(n, b):
         h = torch.randn(n, dtype=torch.complex64, device=dev)
-        for bmin, bmax, b in buckets:
-            while n * b * 8 > MAX_BYTES and b > 1:
-                b //= 2
-            xs, ys = _ring(torch, dev, n, b)
-            k = len(xs)
-            times = {}
-            cs = stream.cuda_stream
-            names = filter_candidates(n)
+        return lambda p, x, y: fft_exec_matched_filter(p.handle, x.data_ptr(), h.data_ptr(), y.data_ptr(), cs)
 
-            def timed(name, factor=1):
-                p = Plan(n, b, FFT_FORWARD, FFT_ALGO_SINGLE_PASS, name)
-                t = _time(torch, stream,
-                          lambda i: fft_exec_matched_filter(p.handle, xs[i % k].data_ptr(),
-                                                            h.data_ptr(), ys[i % k].data_ptr(), cs),
-                          iters * factor)
-                p.close()
-                return t
-
-            for name in names:
-                times[name] = timed(name)
-            best = _pick(times, lambda name: timed(name, FINAL_FACTOR))
-            log(f"tune filter n={n} batch={b} -> {best} {times[best]:.2f} us")
-            entries.append({"n": n, "batch_min": bmin, "batch_max": bmax, "variant": best,
-                            "timed_batch": b, "us": round(times[best], 3),
-                            "candidates": {k2: round(v, 3) for k2, v in times.items()}})
-            del xs, ys
-    return entries
+    return _tune_table(torch, stream, sizes, buckets, iters, log, "filter", 8,
+                       lambda n, b: _ring(torch, dev, n, b), filter_candidates, _single_plan, launch)
 
 
 def tune_fused(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=print):
     """The fused forward -> weight -> adjoint kernel (gradient and loss total
     included) per length and batch bucket, over the single-pass variants."""
-    entries = []
-    for n in sizes:
+    cs = stream.cuda_stream
+
+    def launch(n, b):
         w = torch.rand(n, dtype=torch.float32, device=dev)
         total = torch.empty(1, dtype=torch.float32, device=dev)
-        for bmin, bmax, b in buckets:
-            while n * b * 8 > MAX_BYTES and b > 1:
-                b //= 2
-            xs, ys = _ring(torch, dev, n, b)
-            k = len(xs)
-            rows = torch.empty(b, dtype=torch.float32, device=dev)
-            times = {}
-            cs = stream.cuda_stream
-            names = fused_candidates(n)
+        rows = torch.empty(b, dtype=torch.float32, device=dev)
+        return lambda p, x, y: fft_exec_spectral_energy(p.handle, x.data_ptr(), w.data_ptr(), 0, y.data_ptr(),
+                                                        rows.data_ptr(), total.data_ptr(), cs)
 
-            def timed(name, factor=1):
-                p = Plan(n, b, FFT_FORWARD, FFT_ALGO_SINGLE_PASS, name)
-                t = _time(torch, stream,
-                          lambda i: fft_exec_spectral_energy(
-                              p.handle, xs[i % k].data_ptr(), w.data_ptr(), 0,
-                              ys[i % k].data_ptr(), rows.data_ptr(), total.data_ptr(), cs),
-                          iters * factor)
-                p.close()
-                return t
-
-            for name in names:
-                times[name] = timed(name)
-            best = _pick(times, lambda name: timed(name, FINAL_FACTOR))
-            log(f"tune fused n={n} batch={b} -> {best} {times[best]:.2f} us")
-            entries.append({"n": n, "batch_min": bmin, "batch_max": bmax, "variant": best,
-                            "timed_batch": b, "us": round(times[best], 3),
-                            "candidates": {k2: round(v, 3) for k2, v in times.items()}})
-            del xs, ys
-    return entries
+    return _tune_table(torch, stream, sizes, buckets, iters, log, "fused", 8,
+                       lambda n, b: _ring(torch, dev, n, b), fused_candidates, _single_plan, launch)
 
 
 def tune_storage16(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=print):
@@ -256,36 +260,17 @@ def tune_storage16(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, l
     length and batch bucket, over every single-pass variant.  The bfloat16
     format runs the same kernels with another conversion, so it shares the
     choice.  Half the bytes move, so the best shape can differ from FP32's."""
-    entries = []
-    for n in sizes:
-        for bmin, bmax, b in buckets:
-            while n * b * 4 > MAX_BYTES and b > 1:
-                b //= 2
-            k = max(2, math.ceil(RING_BYTES / (2 * n * b * 4)))
-            xs = [torch.randn(b, n, 2, device=dev).to(torch.float16) for _ in range(k)]
-            ys = [torch.empty_like(xs[0]) for _ in range(k)]
-            times = {}
-            cs = stream.cuda_stream
-            names = [nm for nm, algo in candidates(n) if algo == FFT_ALGO_SINGLE_PASS]
+    cs = stream.cuda_stream
 
-            def timed(name, factor=1):
-                p = Plan(n, b, FFT_FORWARD, FFT_ALGO_SINGLE_PASS, name)
-                t = _time(torch, stream,
-                          lambda i: fft_exec_io(p.handle, xs[i % k].data_ptr(), ys[i % k].data_ptr(),
-                                                FFT_IO_C16, cs),
-                          iters * factor)
-                p.close()
-                return t
+    def ring(n, b):
+        k = _ring_size(n * b * 4)
+        return (list(torch.randn(k, b, n, 2, dtype=torch.float16, device=dev)),
+                list(torch.empty(k, b, n, 2, dtype=torch.float16, device=dev)))
 
-            for name in names:
-                times[name] = timed(name)
-            best = _pick(times, lambda name: timed(name, FINAL_FACTOR))
-            log(f"tune storage16 n={n} batch={b} -> {best} {times[best]:.2f} us")
-            entries.append({"n": n, "batch_min": bmin, "batch_max": bmax, "variant": best,
-                            "timed_batch": b, "us": round(times[best], 3),
-                            "candidates": {k2: round(v, 3) for k2, v in times.items()}})
-            del xs, ys
-    return entries
+    return _tune_table(torch, stream, sizes, buckets, iters, log, "storage16", 4, ring,
+                       lambda n: [nm for nm, algo in candidates(n) if algo == FFT_ALGO_SINGLE_PASS], _single_plan,
+                       lambda n, b: lambda p, x, y: fft_exec_io(p.handle, x.data_ptr(), y.data_ptr(),
+                                                                FFT_IO_C16, cs))
 
 
 def tune_ragged(torch, dev, stream, sizes=None, iters=20, sweeps=2, log=print):
@@ -312,8 +297,8 @@ def tune_ragged(torch, dev, stream, sizes=None, iters=20, sweeps=2, log=print):
         for n, sh in choice.items():
             fft_tune_set_ragged(n, sh)
         p = RaggedPlan(sizes)
-        us = _time(torch, stream, lambda i: p.exec(xs[i % k].data_ptr(), ys[i % k].data_ptr(), cs),
-                   iters)
+        us = _time(torch, stream,
+                   lambda i: p.exec_direct(xs[i % k].data_ptr(), ys[i % k].data_ptr(), cs), iters)
         p.close()
         return us
 
