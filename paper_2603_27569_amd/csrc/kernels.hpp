@@ -520,7 +520,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
   if constexpr (S::T > 64) {
     if ((tid & 63) == 0) red[tid >> 6] = acc;
   }
-  __syncthreads();  // forward passes done with LDS; wave partials visible
+  transform_sync<S>();  // forward passes done with LDS; wave partials visible
   if (t == 0 && live) {
     float total = acc;
     if constexpr (S::T > 64) {
@@ -701,7 +701,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_matched_filter(const c32
     const c32 y = cmulc(a[m], hq);
     a[m] = c32{y.x * inv_n, y.y * inv_n};
   }
-  __syncthreads();
+  transform_sync<S>();
   run_passes<S, true>(a, lds, tw, t);
   buffer_store_row<S>(a, Buf(out + row0 * S::N), slot * S::N, t, live);
 }

@@ -12,7 +12,8 @@
 // of each length in a small per-workgroup table; the kernel needs no device
 // atomic or queue.
 //
-// A workgroup runs its tasks one after another; the second workgroup on the
+// A workgroup runs its tasks one after another (a wave its transforms of up to
+// 64 lanes, without waiting for the workgroup's other waves); the second workgroup on the
 // CU overlaps its loads and stores with this one's arithmetic (measured
 // faster on MI355X than one software-pipelined workgroup per CU holding two
 // tasks in registers).  The next task's descriptor and row offsets are
@@ -39,18 +40,28 @@ constexpr int kClasses = 7;  // lengths 256 << c, c = 0..6
 
 // Two candidate shapes per length, all 512 lanes, at most 128 VGPRs (two
 // workgroups per CU) and at most an 8192-element (+ pad) exchange tile.
-// A: 32 values per lane, two-round exchanges, 16384 elements per task (for
-// 256: 8 values per lane, radix 8 8 4, 4096 elements per task -- 64 tasks of
-// 8 lanes at 32 values needed more than 128 VGPRs and spilled).
+// A: 32 values per lane, exchanges in two rounds or in two parts, 16384
+// elements per task (for 256: 8 values per lane, radix 8 8 4, 4096 elements
+// per task -- 64 tasks of 8 lanes at 32 values needed more than 128 VGPRs and
+// spilled).  8192 and 16384 run three passes (radix 32 first) with split
+// exchanges, where two rounds allow radix 16 at most and take four.
 // B: 16 values per lane, whole-tile exchanges, 8192 elements per task (for
 // 16384, B is the radix-16 order of the A shape).
+//
+// What bounds a task: its loads, arithmetic and stores follow one another,
+// and only the other workgroup on the CU fills the gaps, so a lane waits less
+// the fewer exchanges there are and the fewer lanes a barrier joins.  A full
+// task of 16384 elements, us on an MI355X (two workgroups per CU, every CU
+// busy), before -> with radix 32, row offsets in scalar registers and no
+// barriers between transforms of one wave: 512 29.6 -> 26.1, 1024 29.1 -> 26.5,
+// 2048 28.4 -> 26.4, 8192 31.2 -> 27.4, 16384 31.3 -> 28.8.
 using A256 = ShapeX<1, false, 4, 256, 8, 16, 4, 8, 8, 4>;
 using A512 = ShapeX<2, false, 4, 512, 32, 32, 4, 16, 16, 2>;
 using A1024 = ShapeX<2, false, 4, 1024, 32, 16, 4, 16, 16, 4>;
 using A2048 = ShapeX<2, false, 4, 2048, 32, 8, 4, 16, 16, 8>;
 using A4096 = ShapeX<2, false, 4, 4096, 32, 4, 4, 16, 16, 16>;
-using A8192 = ShapeX<2, false, 4, 8192, 32, 2, 4, 16, 16, 16, 2>;
-using A16384 = ShapeX<2, false, 4, 16384, 32, 1, 4, 8, 16, 16, 8>;
+using A8192 = SplitExchange<ShapeX<1, false, 4, 8192, 32, 2, 5, 32, 16, 16>>;
+using A16384 = SplitExchange<ShapeX<1, false, 4, 16384, 32, 1, 5, 32, 32, 16>>;
 using B256 = ShapeX<1, false, 4, 256, 16, 32, 4, 16, 16>;
 using B512 = ShapeX<1, false, 4, 512, 16, 16, 4, 16, 16, 2>;
 using B1024 = ShapeX<1, false, 4, 1024, 16, 8, 4, 16, 16, 4>;
@@ -82,7 +93,7 @@ const ShapeInfo kShapes[kNumShapes] = {
     info<A2048>("ragged_n2048_e32c2"),     info<B2048>("ragged_n2048_e16"),
     info<A4096>("ragged_n4096_e32c2"),     info<B4096>("ragged_n4096_e16"),
     info<A8192>("ragged_n8192_e32c2"),     info<B8192>("ragged_n8192_e16"),
-    info<A16384>("ragged_n16384_e32c2_r8"), info<B16384>("ragged_n16384_e32c2_r16"),
+    info<A16384>("ragged_n16384_e32c2_r32"), info<B16384>("ragged_n16384_e32c2_r16"),
 };
 
 // Duration of one full task of each shape in microseconds on an MI355X: a
@@ -90,13 +101,13 @@ const ShapeInfo kShapes[kNumShapes] = {
 // CU, every CU busy), kernel time x 512 / 4096.  The list schedule uses them
 // as task costs; only their ratios matter to it.
 constexpr float kShapeTaskUs[kNumShapes] = {
-    7.38f, 13.76f,   // 256
-    29.60f, 14.43f,  // 512
-    29.07f, 14.09f,  // 1024
-    28.39f, 14.41f,  // 2048
-    28.27f, 14.77f,  // 4096
-    31.17f, 16.07f,  // 8192
-    31.26f, 31.47f,  // 16384
+    7.85f, 14.48f,   // 256
+    26.09f, 13.50f,  // 512
+    26.48f, 13.55f,  // 1024
+    26.36f, 14.61f,  // 2048
+    28.70f, 14.94f,  // 4096
+    27.39f, 15.71f,  // 8192
+    28.79f, 30.58f,  // 16384
 };
 
 struct Task {
@@ -118,6 +129,48 @@ struct RaggedArgs {
   const c32* tw[kClasses];  // twiddle table of the chosen shape
 };
 
+// A transform of whole waves has one row offset per wave: held in scalar
+// registers, with its row behind a buffer descriptor, it costs no vector
+// registers or address arithmetic.
+template <class S>
+constexpr bool wave_rows() {
+  return S::T % 64 == 0;
+}
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((uint64_t)v >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+template <class S>
+__device__ __forceinline__ void ragged_load(c32 (&a)[S::E], const c32* row, int t, int stream) {
+  if constexpr (wave_rows<S>()) {
+    const Buf b(row);
+    if (stream) {  // uniform
+#pragma unroll
+      for (int m = 0; m < S::E; ++m) {
+        const u32x2 v = b.ld64<kNT>(8 * t, 8 * m * S::T);
+        a[m] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+      }
+    } else {
+#pragma unroll
+      for (int m = 0; m < S::E; ++m) {
+        const u32x2 v = b.ld64(8 * t, 8 * m * S::T);
+        a[m] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+      }
+    }
+  } else {
+    global_load_row<S>(a, row, t, stream);
+  }
+}
+template <class S>
+__device__ __forceinline__ void ragged_store(const c32 (&a)[S::E], c32* row, int t, bool live) {
+  if constexpr (wave_rows<S>())
+    buffer_store_row<S>(a, Buf(row), 0, t, live);
+  else
+    global_store_row<S>(a, row, t, live);
+}
+
 // Runs this workgroup's tasks [pos, end) of one length one after another (no
 // prefetch of rows; a second resident workgroup overlaps its loads instead).
 // The next task's descriptor and row offsets are loaded while the current
@@ -127,18 +180,21 @@ __device__ __forceinline__ void run_class_serial(int pos, int end, const RaggedA
                                                  c32* lds_all, const c32* tw) {
   static_assert(S::THREADS == kRaggedThreads, "ragged shapes use 512 lanes");
   static_assert(S::TPB * S::LDS_ELEMS <= kLdsElems, "shape exceeds the exchange tile");
-  if (pos >= end) return;
+  if (pos >= end) return;  // uniform
+  __syncthreads();         // the previous length's transforms are done with the exchange tile
   const int tid = threadIdx.x;
-  const int slot = tid / S::T;
+  int slot = S::TPB == 1 ? 0 : tid / S::T;
   const int t = tid - slot * S::T;
+  if constexpr (wave_rows<S>()) slot = __builtin_amdgcn_readfirstlane(slot);
   Task tc = A.tasks[pos];
   int64_t off = slot < tc.count ? A.item_off[tc.first + slot] : 0;
+  if constexpr (wave_rows<S>()) off = uniform64(off);
   for (;;) {
     const bool live = slot < tc.count;
     c32 a[S::E];
     // A dead slot (off = 0) reads the buffer's first N elements, which exist:
     // a length class has a task only if an item of that length does.
-    global_load_row<S>(a, A.in + off, t, A.stream);
+    ragged_load<S>(a, A.in + off, t, A.stream);
     const bool more = pos + 1 < end;
     Task tn = tc;
     int64_t off_n = 0;
@@ -153,12 +209,13 @@ __device__ __forceinline__ void run_class_serial(int pos, int end, const RaggedA
     int tl = t;
     asm volatile("" : "+s"(twl), "+v"(tl));
     run_passes<S, INV>(a, lds_all + slot * S::LDS_ELEMS, twl, tl);
-    global_store_row<S>(a, A.out + off, t, live);
-    __syncthreads();  // the task's last exchange reads are done before the next task writes
+    ragged_store<S>(a, A.out + off, t, live);
+    transform_sync<S>();  // the task's last exchange reads are done before the next task writes
     if (!more) return;
     ++pos;
     tc = tn;
     off = off_n;
+    if constexpr (wave_rows<S>()) off = uniform64(off);  // only now: the load has had a whole task to arrive
   }
 }
 
@@ -187,6 +244,8 @@ __global__ __launch_bounds__(kRaggedThreads, 4) void k_ragged(RaggedArgs A) {
 }
 
 int shape_index(const char* name) {
+  // The 16384-point radix-8 order, which the radix-32 one replaced.
+  if (std::strcmp(name, "ragged_n16384_e32c2_r8") == 0) name = "ragged_n16384_e32c2_r32";
   for (int i = 0; i < kNumShapes; ++i)
     if (std::strcmp(kShapes[i].name, name) == 0) return i;
   return -1;
@@ -194,7 +253,7 @@ int shape_index(const char* name) {
 
 // Built-in per-length shape: the autotuner's choice on MI355X (the package's
 // tune_gfx950.json).
-constexpr int kBuiltinShape[kClasses] = {1, 2, 4, 6, 8, 11, 13};
+constexpr int kBuiltinShape[kClasses] = {0, 2, 4, 6, 9, 10, 12};
 int builtin_shape(int64_t n) { return kBuiltinShape[ilog2(n) - 8]; }
 
 std::mutex g_rtune_mu;

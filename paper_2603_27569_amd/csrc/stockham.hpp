@@ -297,6 +297,22 @@ struct double_buffered : std::false_type {};
 template <class S>
 struct double_buffered<S, std::void_t<decltype(S::DB)>> : std::integral_constant<bool, S::DB> {};
 
+// Split exchange: every exchange sends the real parts of the whole transform
+// through the LDS, then the imaginary parts: half the space like two rounds
+// (C = 2), but without a condition on the radices, so that a radix-32 pass can
+// precede it where a lane holds 32 values.
+template <class Base>
+struct SplitExchange : Base {
+  static_assert(Base::C == 1 && Base::PADLOG > 0, "whole-transform exchanges in the padded layout");
+  static constexpr bool SPLIT = true;
+  static constexpr int LDS_ELEMS = (Base::LDS_ELEMS + 1) / 2;
+};
+
+template <class S, class = void>
+struct split_exchange : std::false_type {};
+template <class S>
+struct split_exchange<S, std::void_t<decltype(S::SPLIT)>> : std::integral_constant<bool, S::SPLIT> {};
+
 // Paired twiddle table: in every pass of radix R >= 4 the twiddles for
 // r = 2q + 1 and 2q + 2 sit side by side, entry [q][k] = (W^{k (2q + 1)},
 // W^{k (2q + 2)}) with W = W_{Ns R} (the last pair holds W^{k (R - 1)} and a
@@ -427,9 +443,50 @@ __device__ __forceinline__ void fetch_twiddles(c32 (&dst)[CAP], int off, const c
   }
 }
 
+// The twiddles of legs r0 + 1 .. r0 + STEP (those that exist) of the same
+// butterfly, into dst[0 .. STEP - 1]; r0 even, STEP even.
+template <class S, int p, int STEP>
+__device__ __forceinline__ void fetch_twiddle_step(c32 (&dst)[STEP], const c32* twp, int k, int r0) {
+  constexpr int R = S::radix(p);
+  constexpr int NS = S::ns(p);
+  static_assert(R >= 4 && STEP % 2 == 0, "whole pairs");
+  const Buf tb(twp);
+  if constexpr (paired_twiddles<S>::value) {
+#pragma unroll
+    for (int i = 0; i < STEP; i += 2) {
+      const u32x4 v = tb.ld128(16 * k, 16 * ((r0 + i) / 2) * NS);
+      dst[i] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+      dst[i + 1] = c32{__uint_as_float(v.z), __uint_as_float(v.w)};
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < STEP; ++i)
+      if (r0 + i + 1 < R) {
+        const u32x2 v = tb.ld64(8 * k, 8 * (r0 + i) * NS);
+        dst[i] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+      }
+  }
+}
+
 // The common case: whole-transform exchange buffer, twiddles one pass ahead.
 template <int N_, int E_, int TPB_, int PADLOG_, int... Rs>
 using Shape = ShapeX<1, true, 1, N_, E_, TPB_, PADLOG_, Rs...>;
+
+// Orders the LDS accesses of one transform's lanes.  Up to 64 lanes they are
+// one wave's, which the LDS executes in order: only the compiler has to keep
+// the order, and the waves of a workgroup that runs several transforms need
+// not wait for each other.  A wider transform takes the workgroup's barrier.
+template <class S>
+__device__ __forceinline__ void transform_sync() {
+  if constexpr (S::T <= 64) {
+    static_assert(64 % S::T == 0, "a transform's lanes lie in one wave");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
 
 // ------------------------------------------------------------ one pass
 
@@ -472,10 +529,28 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
 #pragma unroll
       for (int r = 0; r < R; ++r) v[r] = a[b + r * BPT];
       if constexpr (p > 0) {
-        c32 wb[R - 1];
-        fetch_twiddles<S, p>(wb, 0, tw + S::tw_off(p), bfly_index<S, p>(t, b) & (NS - 1));
+        // With split exchanges (held to 128 VGPRs) a radix-32 butterfly takes
+        // its twiddles eight at a time: all 31 beside the 32 values would
+        // spill.  Where registers are left one round trip for all is faster
+        // (matched filter 16384 x 500: 41.9 against 44.1 us).
+        const int k = bfly_index<S, p>(t, b) & (NS - 1);
+        if constexpr (R > 16 && split_exchange<S>::value) {
+          constexpr int STEP = 8;
 #pragma unroll
-        for (int r = 1; r < R; ++r) v[r] = ctw<INV>(v[r], wb[r - 1]);
+          for (int r0 = 0; r0 < R; r0 += STEP) {
+            c32 wb[STEP];
+            fetch_twiddle_step<S, p>(wb, tw + S::tw_off(p), k, r0);
+#pragma unroll
+            for (int i = 0; i < STEP; ++i)
+              if (r0 + i + 1 < R) v[r0 + i + 1] = ctw<INV>(v[r0 + i + 1], wb[i]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          c32 wb[R - 1];
+          fetch_twiddles<S, p>(wb, 0, tw + S::tw_off(p), k);
+#pragma unroll
+          for (int r = 1; r < R; ++r) v[r] = ctw<INV>(v[r], wb[r - 1]);
+        }
       }
       Dft<R, INV>::run(v);
 #pragma unroll
@@ -531,6 +606,27 @@ __device__ __forceinline__ void exchange_write(const c32 (&a)[S::E], c32* lds, i
   }
 }
 
+// One part (real or imaginary) of every value of a split exchange: written to
+// its Stockham position in 4-byte slots, read at t + m T.
+template <class S, int p, float c32::*PART>
+__device__ __forceinline__ void exchange_part(const c32 (&a)[S::E], c32 (&nxt)[S::E], float* f, int t) {
+  constexpr int R = S::radix(p);
+  constexpr int NS = S::ns(p);
+  constexpr int BPT = S::E / R;
+  const auto wpos = [](int j) { return (j / NS) * NS * R + (j & (NS - 1)); };
+  const int l = wpos(t);
+#pragma unroll
+  for (int b = 0; b < BPT; ++b)
+#pragma unroll
+    for (int k = 0; k < R; ++k) f[S::pidx(l, wpos(b * S::T) + k * NS)] = a[b + k * BPT].*PART;
+  transform_sync<S>();
+#pragma unroll
+  for (int m = 0; m < S::E; ++m) nxt[m].*PART = f[S::pidx(t, m * S::T)];
+  if constexpr (kLdsPoison)
+#pragma unroll
+    for (int m = 0; m < S::E; ++m) f[S::pidx(t, m * S::T)] = __builtin_nanf("");
+}
+
 // Exchange after pass p: write the outputs to their Stockham positions and
 // read the next pass's inputs (positions t + m T, or the paired order when the
 // next pass is a paired last pass), in C rounds of N/C elements.  The buffer
@@ -548,9 +644,20 @@ __device__ __forceinline__ void exchange(c32 (&a)[S::E], c32* lds, int t) {
   static_assert(!PW || S::C == 1 || S::T % S::C == 0, "paired rounds split by lanes");
   static_assert(!PR || S::C == 1 || S::radix(p + 1) % S::C == 0, "paired rounds split by legs");
   c32 nxt[S::E];
+  if constexpr (split_exchange<S>::value) {
+    static_assert(!paired_lanes<S>::value && !double_buffered<S>::value, "split exchanges stand alone");
+    float* f = reinterpret_cast<float*>(lds);
+    exchange_part<S, p, &c32::x>(a, nxt, f, t);
+    transform_sync<S>();  // the real parts are read
+    exchange_part<S, p, &c32::y>(a, nxt, f, t);
+#pragma unroll
+    for (int m = 0; m < S::E; ++m) a[m] = nxt[m];
+    if constexpr (p + 2 < S::P) transform_sync<S>();
+    return;
+  }
 #pragma unroll
   for (int h = 0; h < S::C; ++h) {
-    if (h > 0) __syncthreads();  // the previous round's reads are done
+    if (h > 0) transform_sync<S>();  // the previous round's reads are done
     if constexpr (PW) {
       // Lane t's butterflies all fall in chunk t / (T / C).
       if (S::C == 1 || t / (S::T / S::C) == h) {
@@ -561,7 +668,7 @@ __device__ __forceinline__ void exchange(c32 (&a)[S::E], c32* lds, int t) {
 #pragma unroll
       for (int b = h * BPC; b < (h + 1) * BPC; ++b) exchange_write<S, p>(a, lds, t, b, h * S::CHUNK);
     }
-    __syncthreads();
+    transform_sync<S>();
     if constexpr (PR) {
       const auto at = [&](int m) {
         return S::pidx(read_position<S, p + 1>(t, 0), read_position<S, p + 1>(0, m) - h * S::CHUNK);
@@ -591,7 +698,7 @@ __device__ __forceinline__ void exchange(c32 (&a)[S::E], c32* lds, int t) {
 #pragma unroll
   for (int m = 0; m < S::E; ++m) a[m] = nxt[m];
   if constexpr (p + 2 < S::P && !double_buffered<S>::value)
-    __syncthreads();  // all reads done before the next overwrite
+    transform_sync<S>();  // all reads done before the next overwrite
 }
 
 // Phase marks of the pass pipeline.  The product kernels take NoProbe,
@@ -615,7 +722,7 @@ __device__ __forceinline__ void run_passes_from(c32 (&a)[S::E], c32 (&w)[S::TW_R
     // buffered) starts as NaNs.
 #pragma unroll 1
     for (int i = t; i < S::LDS_ELEMS; i += S::T) lds[i] = lds_poison();
-    __syncthreads();
+    transform_sync<S>();
   }
   pass_compute<S, p, INV>(a, w, tw, t);
   if constexpr (Pr::on) pr->mark(2 * p + 1);
