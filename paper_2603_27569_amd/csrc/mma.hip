@@ -26,8 +26,6 @@
 // parts in accumulators 0 .. 7 and imaginary parts in 8 .. 15.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "internal.hpp"
 #include "kernels.hpp"
 
@@ -58,25 +56,6 @@ struct MmaPlan {
 
 __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
 
-// cos(2 pi m / 16), m = 0 .. 15, from the FP64 values; sin(2 pi m / 16) is
-// entry (m + 12) mod 16.
-__device__ __forceinline__ float cos16(int m) {
-  constexpr float c1 = 0.92387953251128674, c2 = 0.70710678118654757, c3 = 0.38268343236508978;
-  constexpr float t[16] = {1.f, c1, c2, c3, 0.f, -c3, -c2, -c1, -1.f, -c1, -c2, -c3, 0.f, c3, c2, c1};
-  return t[m & 15];
-}
-
-// Entry (i, q) of M (rows: real bins 0..15, imaginary bins 16..31; columns:
-// real legs, imaginary legs).
-template <bool INV>
-__device__ __forceinline__ float dft_entry(int i, int q) {
-  const int m = ((i & 15) * (q & 15)) & 15;
-  const float c = cos16(m);
-  const float s = INV ? -cos16(m + 12) : cos16(m + 12);
-  if (i < 16) return q < 16 ? c : s;
-  return q < 16 ? -s : c;
-}
-
 // The 16-bit operand format: binary16 storage multiplies binary16 operands,
 // bfloat16 storage bfloat16 operands.
 template <class IO>
@@ -84,13 +63,8 @@ struct MmaOps;
 
 template <>
 struct MmaOps<IoF16> {
+  typedef _Float16 E;
   typedef f16x8 V;
-  __device__ __forceinline__ static V pack(const float (&v)[8]) {
-    V r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = (_Float16)v[e];
-    return r;
-  }
   __device__ __forceinline__ static f32x16 mma(V a, V b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
@@ -98,20 +72,36 @@ struct MmaOps<IoF16> {
 
 template <>
 struct MmaOps<IoBF16> {
+  typedef __bf16 E;
   typedef bf16x8 V;
-  __device__ __forceinline__ static V pack(const float (&v)[8]) {
-    V r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = (__bf16)v[e];
-    return r;
-  }
   __device__ __forceinline__ static f32x16 mma(V a, V b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 };
 
-// Bin of the butterfly held in output slot q (q < 8) by half h of the wave.
-__device__ __forceinline__ int out_bin(int q, int h) { return 4 * h + q + (q & 4); }
+// M as the two A operands, one 32-byte record per lane: row l % 32, columns
+// 8 (l / 32) + e (real legs, first product), then 16 + 8 (l / 32) + e.  Two
+// 16-byte loads per lane from a 2 KiB table that stays in the caches, in
+// flight with the first rows; formed from cosines in registers it took a
+// lookup, a sign and a conversion for each of the 16 entries.
+template <class IO, bool INV>
+struct DftMatrix {
+  alignas(16) typename MmaOps<IO>::E e[64][16];
+  constexpr DftMatrix() : e() {
+    // cos(2 pi m / 16) from the FP64 values; sin(2 pi m / 16) is entry m + 12.
+    constexpr float c1 = 0.92387953251128674, c2 = 0.70710678118654757, c3 = 0.38268343236508978;
+    constexpr float t[16] = {1.f, c1, c2, c3, 0.f, -c3, -c2, -c1, -1.f, -c1, -c2, -c3, 0.f, c3, c2, c1};
+    for (int l = 0; l < 64; ++l)
+      for (int i = 0; i < 16; ++i) {
+        const int row = l & 31, leg = 8 * (l >> 5) + (i & 7), m = (row & 15) * leg & 15;
+        const float c = t[m], s = INV ? -t[(m + 12) & 15] : t[(m + 12) & 15];
+        const bool re_row = row < 16, re_leg = i < 8;
+        e[l][i] = (typename MmaOps<IO>::E)(re_row == re_leg ? c : re_row ? s : -s);
+      }
+  }
+};
+template <class IO, bool INV>
+__device__ const DftMatrix<IO, INV> kDftMatrix{};
 
 // The 8 real parts (lo) or imaginary parts (hi) of 8 stored 16-bit pairs as
 // one operand: dword i of the operand is half 0 or 1 of pairs 2i and 2i + 1.
@@ -124,19 +114,65 @@ __device__ __forceinline__ V gather_halves(const uint32_t (&d)[8], bool hi) {
   return __builtin_bit_cast(V, w);
 }
 
+// Twiddles of the 8 bins that lane half h holds of pass p's butterfly j.  Bin
+// k goes to x = (j / Ns) Ns 16 + j mod Ns + k Ns.  The next pass (radix R',
+// Ns' = 16 Ns, N / R' butterflies) reads it as leg r' = x / (N / R') of
+// butterfly j' = x mod (N / R'), whose twiddle there is W_{Ns' R'}^{r' (j' mod
+// Ns')}: table entry tw_off + (r' - 1) Ns' + j' mod Ns'.  k Ns never carries
+// into r' or out of j' mod Ns', so all bins of a butterfly share r' and their
+// entries lie k Ns apart: one lane offset, constant steps, and for Ns = 1 two
+// bins in one 16-byte load.  Leg 0 has no entry: it reads leg 1's and takes 1
+// instead.
+template <class M>
+__device__ __forceinline__ void next_twiddles(c32 (&wn)[8], const char* table, int p, int j, int h) {
+  const int ns = p == 0 ? 1 : p == 1 ? 16 : 256;
+  const bool last16 = p + 1 == M::P;
+  if (last16 && M::RL == 1) return;
+  const int nsn = 16 * ns;
+  const int span = last16 ? M::NL : M::NB;  // N / R' (a power of two)
+  const int off = M::tw_off(p + 1);
+  const int base = (j / ns) * ns * 16 + (j & (ns - 1));
+  const int r = base / span;
+  const unsigned voff = 8u * ((r > 0 ? r - 1 : 0) * nsn + (base & (nsn - 1)) + 4 * h * ns);
+  if (ns == 1) {
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(table + 8 * (off + q + (q & 4)) + voff);
+      wn[q] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+      wn[q + 1] = c32{__uint_as_float(v.z), __uint_as_float(v.w)};
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const u32x2 v = *reinterpret_cast<const u32x2*>(table + 8 * (off + (q + (q & 4)) * ns) + voff);
+      wn[q] = c32{__uint_as_float(v.x), __uint_as_float(v.y)};
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) wn[q] = r > 0 ? wn[q] : c32{1.f, 0.f};
+}
+
+// Waves per SIMD to leave registers for.  Two blocks' products and twiddles
+// fit the 64 registers of 8 waves when the blocks go one after the other
+// (512's unrolled radix-2 pass needs a few more), four together those of 4.
+constexpr int mma_waves(int n, int blocks) { return blocks == 4 ? 4 : n == 512 && blocks == 2 ? 6 : 8; }
+
 // TPWG transforms per workgroup of THREADS lanes, each wave taking kBlocks
-// blocks of 32 butterflies (of one transform or, for short transforms,
-// several): fewer waves per block of work mean more independent products per
-// wave and no barrier waits across waves, more waves fewer registers and more
-// transforms in flight.  One wave per workgroup is held to two waves per SIMD.
+// blocks of 32 butterflies of one transform or, for short transforms, of
+// several.  Bound by the latency of a pass (matrix products of 16 cycles an
+// instruction, an LDS round trip and the twiddles from L1 / L2) until enough
+// waves are in flight, then by memory.
 template <int N, int THREADS, int TPWG, bool INV, class IO>
-__global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma(
-    const uint32_t* in, uint32_t* out, const c32* tw, int64_t rows, int stream) {
+__global__ __launch_bounds__(THREADS, mma_waves(N, TPWG * (N / 512) / (THREADS / 64))) void
+k_stockham_mma(const uint32_t* in, uint32_t* out, const c32* __restrict__ tw, int64_t rows,
+               int stream) {
   using M = MmaPlan<N>;
   constexpr int NB = M::NB;
   constexpr int BPT = NB / 32;  // blocks per transform
   constexpr int kBlocks = TPWG * BPT / (THREADS / 64);
+  static_assert(M::RL > 1 || TPWG == 1, "the last radix-16 pass stores every slot");
   static_assert(kBlocks >= 1 && kBlocks * (THREADS / 64) == TPWG * BPT, "lanes per transform");
+  constexpr int G = kBlocks == 4 ? 4 : 1;  // blocks whose products are in flight together
   using Ops = MmaOps<IO>;
   using V = typename Ops::V;
   __shared__ alignas(16) uint32_t lds[TPWG * M::LDS];  // 16-bit pairs, one pad per 16
@@ -147,28 +183,14 @@ __global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma
   const int64_t row0 = (int64_t)blockIdx.x * TPWG;
   if (row0 >= rows) return;  // whole workgroup, before any barrier
 
-  // The DFT matrix as the A operand: row jl, columns 8h + e (first product,
-  // real legs) and 16 + 8h + e (second product, imaginary legs).
-  V a_re, a_im;
-  {
-    float re[8], im[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      re[e] = dft_entry<INV>(jl, 8 * h + e);
-      im[e] = dft_entry<INV>(jl, 16 + 8 * h + e);
-    }
-    a_re = Ops::pack(re);
-    a_im = Ops::pack(im);
-  }
-
   // Block b of this wave: transform tr[b] of the workgroup, butterfly j[b];
-  // rows past the batch (a last, partial workgroup) compute on zeros and
-  // store nothing.
+  // rows past the batch (a last, partial workgroup) store nothing.
   int j[kBlocks], tr[kBlocks];
   bool live[kBlocks];
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
   for (int b = 0; b < kBlocks; ++b) {
-    const int g = (tid >> 6) * kBlocks + b;
+    const int g = wave * kBlocks + b;
     tr[b] = TPWG > 1 ? g / BPT : 0;
     j[b] = 32 * (g - tr[b] * BPT) + jl;
     live[b] = TPWG == 1 || row0 + tr[b] < rows;  // one transform: row0 < rows
@@ -176,77 +198,68 @@ __global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma
 
   // Legs 8h + e of each butterfly as stored pairs: the first pass takes its
   // operands straight from HBM, the later ones from LDS, where the writer has
-  // already applied their twiddles and rounded.
+  // already applied their twiddles and rounded.  Rows, tables and results go
+  // through buffer descriptors: every access is a lane part plus a constant.
+  // A slot past the last row loads the workgroup's first row instead.
   uint32_t d[kBlocks][8];
+  {
+    const Buf src(in + row0 * N);
 #pragma unroll
-  for (int b = 0; b < kBlocks; ++b) {
-    const uint32_t* src = in + (row0 + tr[b]) * N;
-    if (stream) {
+    for (int b = 0; b < kBlocks; ++b) {
+      const int voff = 4 * ((live[b] ? tr[b] : 0) * N + j[b] + 8 * h * NB);
+      if (stream) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        d[b][e] = live[b] ? __builtin_nontemporal_load(src + j[b] + (8 * h + e) * NB) : 0u;
-    } else {
+        for (int e = 0; e < 8; ++e) d[b][e] = src.ld32<kNT>(voff, 4 * e * NB);
+      } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) d[b][e] = live[b] ? src[j[b] + (8 * h + e) * NB] : 0u;
+        for (int e = 0; e < 8; ++e) d[b][e] = src.ld32(voff, 4 * e * NB);
+      }
     }
   }
+  const V* const m = reinterpret_cast<const V*>(kDftMatrix<IO, INV>.e[lane]);
+  const V a_re = m[0], a_im = m[1];
+  const char* const table = reinterpret_cast<const char*>(tw);
 
 #pragma unroll
   for (int p = 0; p < M::P; ++p) {
     const int ns = 1 << (4 * p);  // Ns of this pass
     const bool last16 = p == M::P - 1;
-    // Bin k of butterfly j goes to x = (j / Ns) Ns 16 + j mod Ns + k Ns.  The
-    // next pass (radix R', Ns' = 16 Ns, N / R' butterflies) reads it as leg
-    // r' = x / (N / R') of butterfly j' = x mod (N / R'), whose twiddle there
-    // is W_{Ns' R'}^{r' (j' mod Ns')}: table entry tw_off + (r' - 1) Ns' + j'
-    // mod Ns'.  Loaded before the products.
-    c32 wn[kBlocks][8];
-    if (!last16 || M::RL > 1) {
-      const int nsn = 16 * ns;
-      const int span = last16 ? M::NL : NB;  // N / R' (a power of two)
-      const int off = M::tw_off(p + 1);
-#pragma unroll
-      for (int b = 0; b < kBlocks; ++b) {
-        const int base = (j[b] / ns) * ns * 16 + (j[b] & (ns - 1));
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int x = base + out_bin(q, h) * ns;
-          const int r = x / span, jn = x & (span - 1);
-          wn[b][q] = r > 0 ? tw[off + (r - 1) * nsn + (jn & (nsn - 1))] : c32{1.f, 0.f};
-        }
-      }
-    }
-    f32x16 acc[kBlocks];
-#pragma unroll
-    for (int b = 0; b < kBlocks; ++b)
-      acc[b] = Ops::mma(a_re, gather_halves<V>(d[b], false), f32x16{});
-#pragma unroll
-    for (int b = 0; b < kBlocks; ++b) acc[b] = Ops::mma(a_im, gather_halves<V>(d[b], true), acc[b]);
-    if (last16 && M::RL == 1) {
-      // Last pass (Ns = N / 16): bin k of butterfly j is element j + k N / 16.
-#pragma unroll
-      for (int b = 0; b < kBlocks; ++b) {
-        if (!live[b]) continue;
-        uint32_t* dst = out + (row0 + tr[b]) * N;
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          __builtin_nontemporal_store(IO::store(c32{acc[b][q], acc[b][8 + q]}),
-                                      dst + j[b] + out_bin(q, h) * NB);
-      }
-      return;
-    }
     // With one pad element per 16 the padded slots are affine in k: pidx(x) =
     // pidx(x at k = 0) + k for Ns = 1 (x = 16 j + k) and + 17 Ns / 16 k for
     // Ns >= 16, so every write is a base address plus a constant.
     const int step = p == 0 ? 1 : 17 * ns / 16;
 #pragma unroll
-    for (int b = 0; b < kBlocks; ++b) {
-      uint32_t* wr = lds + tr[b] * M::LDS + pidx((j[b] / ns) * ns * 16 + (j[b] & (ns - 1))) +
-                     step * 4 * h;
+    for (int b0 = 0; b0 < kBlocks; b0 += G) {
+      c32 wn[G][8];
+      f32x16 acc[G];
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        wr[step * (q + (q & 4))] = IO::store(ctw<INV>(c32{acc[b][q], acc[b][8 + q]}, wn[b][q]));
+      for (int g = 0; g < G; ++g) next_twiddles<M>(wn[g], table, p, j[b0 + g], h);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        acc[g] = Ops::mma(a_re, gather_halves<V>(d[b0 + g], false), f32x16{});
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        acc[g] = Ops::mma(a_im, gather_halves<V>(d[b0 + g], true), acc[g]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int b = b0 + g;
+        if (last16 && M::RL == 1) {
+          // Last pass (Ns = N / 16): bin k of butterfly j is element j + k N / 16.
+          const Buf dst(out + row0 * N);
+          const int voff = 4 * (tr[b] * N + j[b] + 4 * h * NB);
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            dst.st32<kNT>(IO::store(c32{acc[g][q], acc[g][8 + q]}), voff, 4 * (q + (q & 4)) * NB);
+        } else {
+          uint32_t* wr = lds + tr[b] * M::LDS + pidx((j[b] / ns) * ns * 16 + (j[b] & (ns - 1))) +
+                         step * 4 * h;
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            wr[step * (q + (q & 4))] = IO::store(ctw<INV>(c32{acc[g][q], acc[g][8 + q]}, wn[g][q]));
+        }
+      }
     }
+    if (last16 && M::RL == 1) return;
     __syncthreads();
     if (!last16) {
       // pidx(j + r N / 16) = pidx(j) + 17 N / 256 r.
@@ -264,18 +277,20 @@ __global__ __launch_bounds__(THREADS, THREADS == 64 ? 2 : 1) void k_stockham_mma
     // reads legs j + r N / RL (twiddles already applied) and writes bin k to
     // element j + k N / RL.
     constexpr int R = M::RL, NL = M::NL;
+    static_assert(NL % 16 == 0 && (NL % THREADS == 0 || THREADS % NL == 0), "whole pad rows");
+    const Buf dst(out + row0 * N);
 #pragma unroll
     for (int i = tid; i < TPWG * NL; i += THREADS) {
       const int t = i / NL, jb = i - t * NL;
-      if (row0 + t >= rows) continue;
-      const uint32_t* rd = lds + t * M::LDS;
+      if (TPWG > 1 && row0 + t >= rows) continue;
+      const uint32_t* rd = lds + t * M::LDS + pidx(jb);
       c32 v[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = IO::load(rd[pidx(jb + r * NL)]);
+      for (int r = 0; r < R; ++r) v[r] = IO::load(rd[r * (NL + NL / 16)]);
       Dft<R, INV>::run(v);
-      uint32_t* dst = out + (row0 + t) * N;
+      const int voff = 4 * (t * N + jb);
 #pragma unroll
-      for (int k = 0; k < R; ++k) __builtin_nontemporal_store(IO::store(v[k]), dst + jb + k * NL);
+      for (int k = 0; k < R; ++k) dst.st32<kNT>(IO::store(v[k]), voff, 4 * k * NL);
     }
   }
 }
@@ -299,33 +314,49 @@ hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t
   return hipGetLastError();
 }
 
-// Lanes per transform.  N = 4096 by batch, from measurements (binary16,
-// microseconds per launch for 256 / 128 / 64 lanes): batch 256: 5.2 / 5.7 /
-// 7.3, 2048: 23.0 / 17.1 / 17.5, 16384: 152 / 131 / 120.  The bfloat16 kernel
-// needs more registers (its twiddle product and rounding do not fuse), and
-// with one wave per transform it spills: it stops at two waves.  Other
-// lengths (measured at about 64 MiB per launch): up to 2048 one wave per
-// workgroup with four blocks of 32 butterflies (eight spill), so 512 and 1024
-// take several transforms per workgroup (2048: 17.8 against 23.1 us with two
-// waves of two blocks at 2048 x 4096), 8192
-// four blocks per wave (23.1 against 24.3 with two), 16384 two blocks per
-// wave (28.8 against 29.4 with four).
+// Blocks of 32 butterflies per wave, by the blocks of the launch (the chip has
+// 1024 SIMDs).  Device time per launch with 1 / 2 / 4 per wave (4: products
+// together), binary16, input in the Infinity Cache, microseconds:
+//   up to four waves of one block per SIMD a pass's latency decides, and one
+//   block is the shortest chain: 512 x 129 2.25 / 3.2 / 4.9, 2048 x 513 4.1 /
+//   4.9 / 5.4, 4096 x 257 4.6 / 4.8 / 5.8, 8192 x 129 6.5 / 6.8 / 7.6;
+//   beyond, two blocks share the matrix operands and leave fewer waves to
+//   start: 512 x 6145 7.2 / 6.7 / 8.1, 2048 x 4097 16.4 / 15.6 / 16.8, 8192 x
+//   3201 69.6 / 67.5 / 70.7 (with the input in HBM 2048 x 1537 takes 8.9 / 8.3
+//   / 8.5);
+//   512 and 1024 gain from whole transforms per wave once all waves are full
+//   (1024 x 8193 15.9 / 15.7 / 14.2, x 25601 51.6 / 52.1 / 46.3); the other
+//   lengths do not.
+// 16384 has no one-block form (2048 lanes).  The kernel before this one (four
+// blocks, 102 ... 168 registers, 64-bit addresses and the matrix formed in
+// registers) took 6.9 at 512 x 129, 5.6 at 2048 x 513, 5.2 at 4096 x 257, 7.9 at
+// 8192 x 129, 11.7 at 512 x 6145, 19.4 at 2048 x 4097, 19.6 at 1024 x 8193 and
+// 93.2 at 16384 x 1601 (now 70.5).
 template <class IO>
 hipError_t launch_mma(int64_t n, const void* in, void* out, const void* tw, int64_t batch,
                       bool inverse, hipStream_t s) {
-  constexpr bool f16 = std::is_same<IO, IoF16>::value;
+  const int64_t blocks = batch * (n / 512);
+  const bool one = blocks <= 4096, four = blocks > 8192;
   switch (n) {
-    case 512: return launch_mma_threads<512, 64, IO, 4>(in, out, tw, batch, inverse, s);
-    case 1024: return launch_mma_threads<1024, 64, IO, 2>(in, out, tw, batch, inverse, s);
-    case 2048: return launch_mma_threads<2048, 64, IO, 1>(in, out, tw, batch, inverse, s);
-    case 8192: return launch_mma_threads<8192, 256, IO>(in, out, tw, batch, inverse, s);
-    case 16384: return launch_mma_threads<16384, 1024, IO>(in, out, tw, batch, inverse, s);
-    default: break;
+    case 512:
+      if (one) return launch_mma_threads<512, 64, IO, 1>(in, out, tw, batch, inverse, s);
+      if (!four) return launch_mma_threads<512, 64, IO, 2>(in, out, tw, batch, inverse, s);
+      return launch_mma_threads<512, 64, IO, 4>(in, out, tw, batch, inverse, s);
+    case 1024:
+      if (one) return launch_mma_threads<1024, 128, IO>(in, out, tw, batch, inverse, s);
+      if (!four) return launch_mma_threads<1024, 64, IO>(in, out, tw, batch, inverse, s);
+      return launch_mma_threads<1024, 64, IO, 2>(in, out, tw, batch, inverse, s);
+    case 2048:
+      if (one) return launch_mma_threads<2048, 256, IO>(in, out, tw, batch, inverse, s);
+      return launch_mma_threads<2048, 128, IO>(in, out, tw, batch, inverse, s);
+    case 4096:
+      if (one) return launch_mma_threads<4096, 512, IO>(in, out, tw, batch, inverse, s);
+      return launch_mma_threads<4096, 256, IO>(in, out, tw, batch, inverse, s);
+    case 8192:
+      if (one) return launch_mma_threads<8192, 1024, IO>(in, out, tw, batch, inverse, s);
+      return launch_mma_threads<8192, 512, IO>(in, out, tw, batch, inverse, s);
+    default: return launch_mma_threads<16384, 1024, IO>(in, out, tw, batch, inverse, s);
   }
-  if (batch <= 512) return launch_mma_threads<4096, 256, IO>(in, out, tw, batch, inverse, s);
-  if constexpr (f16)
-    if (batch > 4096) return launch_mma_threads<4096, 64, IO>(in, out, tw, batch, inverse, s);
-  return launch_mma_threads<4096, 128, IO>(in, out, tw, batch, inverse, s);
 }
 
 }  // namespace
