@@ -61,54 +61,52 @@ __device__ __forceinline__ c32 mul_w4(c32 a) {
   else return {a.y, -a.x};
 }
 
-// cos/sin of k pi / 8, rounded once from their exact values.
-constexpr float kC1 = 0.923879532511286756128f;  // cos(pi/8)
-constexpr float kS1 = 0.382683432365089771728f;  // sin(pi/8)
-constexpr float kR2 = 0.707106781186547524401f;  // cos(pi/4)
-
-// cos(k pi / 16), any k >= 0, by symmetry from the rounded first-quadrant values.
-constexpr float cos_pi16(int k) {
-  constexpr float q[9] = {1.0f, 0.980785280403230449126f, kC1, 0.831469612302545237079f, kR2,
-                          0.555570233019602224743f, kS1, 0.195090322016128267848f, 0.0f};
+// cos(k pi / 16) and sin(k pi / 16), any k >= 0, by symmetry.
+constexpr double cos_pi16(int k) {
+  constexpr double q[9] = {1.0, 0.980785280403230449126, 0.923879532511286756128,
+                           0.831469612302545237079, 0.707106781186547524401, 0.555570233019602224743,
+                           0.382683432365089771728, 0.195090322016128267848, 0.0};
   k &= 31;
   if (k > 16) k = 32 - k;
   return k <= 8 ? q[k] : -q[16 - k];
 }
-constexpr float sin_pi16(int k) { return cos_pi16(k + 24); }
+constexpr double sin_pi16(int k) { return cos_pi16(k + 24); }
 
-// v * W_R^k for the direction (W = e^{-2 pi i / R} forward, its conjugate
-// backward), with k and R compile-time; exact roots need no multiply.
-template <int R, int K, bool INV>
-__device__ __forceinline__ c32 mul_root(c32 v) {
-  constexpr int k16 = (K * 16 / R) & 15;  // the same root expressed in W_16
-  static_assert((K * 32) % R == 0, "roots beyond W_32 are not tabulated");
-  if constexpr ((K * 16) % R != 0) {  // odd multiples of pi/16
-    constexpr int k32 = K * 32 / R;
-    constexpr float c = cos_pi16(k32);
-    constexpr float s = INV ? sin_pi16(k32) : -sin_pi16(k32);
-    return {c * v.x - s * v.y, c * v.y + s * v.x};
-  } else if constexpr (k16 == 0) {
-    return v;
-  } else if constexpr (k16 == 4) {
-    return mul_w4<INV>(v);
-  } else if constexpr (k16 == 8) {
-    return {-v.x, -v.y};
-  } else if constexpr (k16 == 12) {
-    return mul_w4<!INV>(v);
-  } else if constexpr (k16 == 2 || k16 == 6 || k16 == 10 || k16 == 14) {
-    // (+-r2, +-r2) roots: two multiplies.
-    constexpr float cr = (k16 == 2 || k16 == 14) ? kR2 : -kR2;
-    constexpr float si = (k16 == 2 || k16 == 6) ? -kR2 : kR2;  // forward sign
-    constexpr float s = INV ? -si : si;
-    return {cr * v.x - s * v.y, cr * v.y + s * v.x};
+// The radix-2 butterfly e + W o, e - W o with W = W_R^K = c + i s of the
+// direction, K < R / 2.  Exact roots take four additions.  FUSED: any other
+// root is its larger part times (1, t), |t| <= 1; two fused operations form
+// u = W o / c (or W o / s) and four add and subtract its multiple, six in all
+// where the product first (a multiplication and a fused operation per part)
+// and then the sums take eight, with as many roundings on the way to each
+// result.  A 16-point DFT is 148 operations instead of 168, a 32-point one 388
+// instead of 456.  |u| is at most sqrt(2) |W o|.
+//
+// The fused form is for kernels that the vector units bound (16-bit storage,
+// 42 operations per point and 4 + 4 bytes: binary16 4096 x 2048 14.45 -> 14.2
+// us, 16384 x 500 20.2 -> 18.9; 2000 ragged transforms 37.6 -> 36.3; the
+// two-transform kernels, matched filter 8192 x 300 16.7 -> 16.4).
+// Kernels that stream complex64 rows once keep the product first: memory
+// bounds them, and with the shorter bursts of work between its accesses the
+// chip moved 2 % less (16384 x 1024 52.2 -> 53.3 us, 65536 x 101 36.0 ->
+// 36.4).  Column kernels of 32 values per lane do more work per byte and gain
+// again (2^20 x 16 101.0 -> 100.0).
+template <int R, int K, bool INV, bool FUSED>
+__device__ __forceinline__ void root_butterfly(c32 e, c32 o, c32& plus, c32& minus) {
+  static_assert(32 % R == 0 && K >= 0 && 2 * K < R, "roots beyond W_32 are not tabulated");
+  constexpr int k32 = K * 32 / R;
+  constexpr double c = cos_pi16(k32), s = INV ? sin_pi16(k32) : -sin_pi16(k32);
+  if constexpr (K != 0 && 4 * K != R && FUSED) {
+    constexpr bool by_c = c * c >= s * s;
+    constexpr float t = (float)(by_c ? s / c : c / s), f = (float)(by_c ? c : s);
+    const float ux = by_c ? __builtin_fmaf(-t, o.y, o.x) : __builtin_fmaf(t, o.x, -o.y);
+    const float uy = by_c ? __builtin_fmaf(t, o.x, o.y) : __builtin_fmaf(t, o.y, o.x);
+    plus = {__builtin_fmaf(f, ux, e.x), __builtin_fmaf(f, uy, e.y)};
+    minus = {__builtin_fmaf(-f, ux, e.x), __builtin_fmaf(-f, uy, e.y)};
   } else {
-    // odd multiples of pi/8
-    constexpr float c = (k16 == 1 || k16 == 15) ? kC1 : (k16 == 3 || k16 == 13) ? kS1
-                        : (k16 == 5 || k16 == 11) ? -kS1 : -kC1;
-    constexpr float sf = (k16 == 1 || k16 == 7) ? -kS1 : (k16 == 3 || k16 == 5) ? -kC1
-                         : (k16 == 9 || k16 == 15) ? kS1 : kC1;
-    constexpr float s = INV ? -sf : sf;
-    return {c * v.x - s * v.y, c * v.y + s * v.x};
+    constexpr float cf = (float)c, sf = (float)s;
+    const c32 w = K == 0 ? o : 4 * K == R ? mul_w4<INV>(o) : c32{cf * o.x - sf * o.y, cf * o.y + sf * o.x};
+    plus = cadd(e, w);
+    minus = csub(e, w);
   }
 }
 
@@ -118,11 +116,11 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
 // W_R^k * DFT_{R/2}(odd)).  For R = 8 this is the split DIT butterfly of
 // Section V-B, eq. (4).
 
-template <int R, bool INV>
+template <int R, bool INV, bool FUSED = true>
 struct Dft;
 
-template <bool INV>
-struct Dft<2, INV> {
+template <bool INV, bool FUSED>
+struct Dft<2, INV, FUSED> {
   __device__ __forceinline__ static void run(c32 (&v)[2]) {
     c32 a = v[0], b = v[1];
     v[0] = cadd(a, b);
@@ -130,15 +128,13 @@ struct Dft<2, INV> {
   }
 };
 
-template <int R, bool INV>
+template <int R, bool INV, bool FUSED>
 struct Dft {
   template <int K>
   __device__ __forceinline__ static void combine(c32 (&v)[R], const c32 (&e)[R / 2],
                                                  const c32 (&o)[R / 2]) {
     if constexpr (K < R / 2) {
-      c32 t = mul_root<R, K, INV>(o[K]);
-      v[K] = cadd(e[K], t);
-      v[K + R / 2] = csub(e[K], t);
+      root_butterfly<R, K, INV, FUSED>(e[K], o[K], v[K], v[K + R / 2]);
       combine<K + 1>(v, e, o);
     }
   }
@@ -149,8 +145,8 @@ struct Dft {
       e[i] = v[2 * i];
       o[i] = v[2 * i + 1];
     }
-    Dft<R / 2, INV>::run(e);
-    Dft<R / 2, INV>::run(o);
+    Dft<R / 2, INV, FUSED>::run(e);
+    Dft<R / 2, INV, FUSED>::run(o);
     combine<0>(v, e, o);
   }
 };
@@ -296,6 +292,18 @@ template <class S, class = void>
 struct double_buffered : std::false_type {};
 template <class S>
 struct double_buffered<S, std::void_t<decltype(S::DB)>> : std::integral_constant<bool, S::DB> {};
+
+// Kernels that stream complex64 rows run a shape's passes with products before
+// sums (see root_butterfly).
+template <class Base>
+struct ProductFirst : Base {
+  static constexpr bool PRODUCT_FIRST = true;
+};
+
+template <class S, class = void>
+struct product_first : std::false_type {};
+template <class S>
+struct product_first<S, std::void_t<decltype(S::PRODUCT_FIRST)>> : std::true_type {};
 
 // Split exchange: every exchange sends the real parts of the whole transform
 // through the LDS, then the imaginary parts: half the space like two rounds
@@ -552,7 +560,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
           for (int r = 1; r < R; ++r) v[r] = ctw<INV>(v[r], wb[r - 1]);
         }
       }
-      Dft<R, INV>::run(v);
+      Dft<R, INV, !product_first<S>::value>::run(v);
 #pragma unroll
       for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
     }
@@ -571,7 +579,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
     c32 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = a[b + r * BPT];
-    Dft<R, INV>::run(v);
+    Dft<R, INV, !product_first<S>::value>::run(v);
 #pragma unroll
     for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
   }
