@@ -386,27 +386,25 @@ const BuiltinEntry kBuiltinStorage16[] = {
 // Built-in fused forward -> weight -> adjoint choices: the autotuner's result
 // on MI355X (the "fused_entries" of the package's tune_gfx950.json).
 const BuiltinEntry kBuiltinFused[] = {
-    {256, 1, 160, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 161, 256, "n256_e4_b4_p4_r4.4.4.4"},
-    {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 385, 512, "n256_e4_b4_p4_r4.4.4.4"},
-    {256, 513, 1024, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 1025, 6144, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {256, 1, 2048, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 2049, 6144, "n256_e8_b8_p4_r8.8.4_pt_ol"},
     {256, 6145, 8192, "n256_e16_b16_p4_r16.16_pt"},
     {256, 8193, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt_ol"},
-    {512, 1, 160, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {512, 161, 384, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 385, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {1024, 1, 64, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 65, 160, "n1024_e4_b1_p4_r4.4.4.4.4"},
-    {1024, 161, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
-    {1024, 769, 2048, "n1024_e8_b2_p4_r8.8.8.2_pt"},
-    {1024, 2049, 3072, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
-    {1024, 3073, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
-    {2048, 1, 1024, "n2048_e8_b1_p4_r8.8.8.4_pt"},
-    {2048, 1025, 2048, "n2048_e16_b2_p4_r16.16.8_pt"},
-    {2048, 2049, 4096, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
-    {2048, 4097, INT64_MAX, "n2048_e16_b2_p4_r16.16.8_pt"},
+    {512, 1, 16, "n512_e8_b4_p4_r8.8.8_pt"},
+    {512, 17, 3072, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 3073, 4096, "n512_e8_b4_p4_r8.8.8_pt"},
+    {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {1024, 1, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
+    {1024, 769, 1536, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
+    {1024, 1537, 2048, "n1024_e16_b1_p4_r16.16.4_pt"},
+    {1024, 2049, 3072, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
+    {1024, 3073, 4096, "n1024_e32_b4_p4_r32.32_pt"},
+    {1024, 4097, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
+    {2048, 1, 512, "n2048_e8_b1_p4_r8.8.8.4_pt"},
+    {2048, 513, 1536, "n2048_e16_b1_p4_r16.16.8_pt"},
+    {2048, 1537, 6144, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
+    {2048, 6145, INT64_MAX, "n2048_e16_b1_p4_r16.16.8_pt"},
     {4096, 1, 256, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
     {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt_tall"},
     {4096, 385, 512, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
@@ -415,22 +413,17 @@ const BuiltinEntry kBuiltinFused[] = {
     {4096, 1025, 1536, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
     {4096, 1537, 2048, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
     {4096, 2049, INT64_MAX, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
-    {8192, 1, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 1, 160, "n8192_e16_b1_p4_r16.16.16.2_pt"},
+    {8192, 161, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
     {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
-    {8192, 513, 1024, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
-    {8192, 1025, 1536, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
-    {8192, 1537, 8192, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
-    {8192, 8193, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
+    {8192, 513, 2048, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
+    {8192, 2049, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.16.2_pt"},
     {16384, 1, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
     {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
-    {16384, 257, 512, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
+    {16384, 257, 384, "n16384_e64_c2_b1_p4_r32.32.16_pt_ol"},
+    {16384, 385, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
     {16384, 513, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 769, 1024, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
-    {16384, 1025, 1536, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 1537, 2048, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
-    {16384, 2049, 3072, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 3073, 8192, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
-    {16384, 8193, INT64_MAX, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 769, INT64_MAX, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
 };
 
 // Single-pass fallback when a four-step choice is not wanted.

@@ -402,18 +402,25 @@ __device__ __forceinline__ float wave_group_sum(float v) {
 // The loss total of the fused kernels: the last workgroup to count itself
 // adds all rows in a fixed order (bitwise reproducible), reading them with
 // device-scope atomic loads as they were published, so no cache write-back is
-// needed.  fused_loss_count: thread 0 of a workgroup whose row losses have
-// been published (and have completed) counts it; gi is its index among the
-// groups_all workgroups that count; returns whether it came last.
-__device__ __forceinline__ int fused_loss_count(unsigned* counters, unsigned groups_all, unsigned gi) {
+// needed.  One thread of every workgroup counts it, in two parts so that the
+// counters' round trips pass behind other work: fused_loss_arrive, when the
+// workgroup's row losses have been published (and have completed), adds to
+// the first-level counter; fused_loss_last waits for what it returned, goes
+// on to the second level if need be and returns whether the workgroup came
+// last of the groups_all that count.  gi is its index among them.
+__device__ __forceinline__ unsigned fused_loss_arrive(unsigned* counters, unsigned gi) {
+  return atomicAdd(counters + gi % kTotalGroups * 64, 1u);
+}
+
+__device__ __forceinline__ int fused_loss_last(unsigned arrived, unsigned* counters,
+                                               unsigned groups_all, unsigned gi) {
   const unsigned grp = gi % kTotalGroups;
   const unsigned in_grp = groups_all / kTotalGroups + (grp < groups_all % kTotalGroups ? 1u : 0u);
   const unsigned ngrp = groups_all < kTotalGroups ? groups_all : kTotalGroups;
-  unsigned* c1 = counters + grp * 64;
   unsigned* c2 = counters + kTotalGroups * 64;
   int last = 0;
-  if (atomicAdd(c1, 1u) == in_grp - 1u) {
-    atomicExch(c1, 0u);
+  if (arrived == in_grp - 1u) {
+    atomicExch(counters + grp * 64, 0u);
     if (atomicAdd(c2, 1u) == ngrp - 1u) {
       atomicExch(c2, 0u);
       last = 1;
@@ -433,13 +440,29 @@ __device__ __forceinline__ void fused_loss_sum(float* scratch, float* total_out,
   // v + h for h = 512, 256, ..., 1).  Thread tid plays lanes tid + j THREADS.
   static_assert(1024 % S::THREADS == 0 && S::THREADS % 64 == 0, "lane mapping");
   static_assert(S::TPB * S::LDS_ELEMS * sizeof(c32) >= S::THREADS * sizeof(float), "tree");
-  constexpr int V = 1024 / S::THREADS;
+  // A lane's loads bypass the L2, about a microsecond each: 16 in flight per
+  // thread, added in their order.
+  constexpr int V = 1024 / S::THREADS, U = 16 / V;
   float v[V];
 #pragma unroll
-  for (int j = 0; j < V; ++j) {
-    v[j] = 0.f;
-    for (int64_t i = tid + j * S::THREADS; i < rows_all; i += 1024)
-      v[j] += __hip_atomic_load(row_loss_all + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int j = 0; j < V; ++j) v[j] = 0.f;
+  for (int64_t base = 0; base < rows_all; base += 1024 * U) {
+    float q[U][V] = {};
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (base + 1024 * u >= rows_all) break;  // uniform
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const int64_t i = base + 1024 * u + tid + j * S::THREADS;
+        if (i < rows_all)
+          q[u][j] = __hip_atomic_load(row_loss_all + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < V; ++j)
+        v[j] += q[u][j];  // (a missing row's zero changes nothing: v starts at +0)
   }
 #pragma unroll
   for (int h = V / 2; h > 0; h >>= 1)  // tree steps h * THREADS, inside a thread
@@ -462,18 +485,42 @@ __device__ __forceinline__ void fused_loss_sum(float* scratch, float* total_out,
   if (tid == 0) total_out[0] = part;
 }
 
-// Both steps after the workgroup's last store: every workgroup of the launch
-// calls it once, after publishing its rows.
-template <class S>
-__device__ __forceinline__ void fused_loss_total(float* scratch, int& is_last, float* total_out,
-                                                 unsigned* counters, const float* row_loss_all,
-                                                 int64_t rows_all, unsigned groups_all, unsigned gi) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this lane's publication has completed
-  __syncthreads();  // ... for every lane; and the LDS is free
-  if (threadIdx.x == 0) is_last = fused_loss_count(counters, groups_all, gi);
-  __syncthreads();
-  if (is_last) fused_loss_sum<S>(scratch, total_out, row_loss_all, rows_all);
+// Publishes a row's loss where every XCD sees it.  With RET the exchange
+// returns a value that fused_loss_published waits for, and only for that;
+// without, it waits for all of the wave's accesses.  Both are free where other
+// work has passed since and nothing younger is in flight.
+template <bool RET>
+__device__ __forceinline__ float fused_loss_publish(float* row_loss, float v) {
+  if constexpr (RET) return atomicExch(row_loss, v);
+  atomicExch(row_loss, v);
+  return 0.f;
 }
+template <bool RET>
+__device__ __forceinline__ void fused_loss_published(float returned) {
+  if constexpr (RET)
+    asm volatile("" ::"v"(returned) : "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Counts a workgroup of one transform in the middle of its adjoint, at phase
+// mark AT of the passes: the publication before them has completed by then,
+// and the counter's answer comes during the rest.
+template <int AT>
+struct CountProbe {
+  static constexpr bool on = true;
+  unsigned* counters;
+  unsigned gi;
+  bool counts;  // one thread of the workgroup, the one that published
+  float published;
+  unsigned arrived = 0;
+  __device__ __forceinline__ void mark(int phase) {
+    if (phase == AT && counts) {
+      fused_loss_published<true>(published);
+      arrived = fused_loss_arrive(counters, gi);
+    }
+  }
+};
 
 // -------------------------------------------------- fused forward/adjoint
 // x -> y = F x -> (row loss sum w^2 |y|^2, g = 2 w^2 y * scale) -> F^H g.
@@ -492,6 +539,10 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
   __shared__ alignas(16) c32 lds_all[S::TPB * S::LDS_ELEMS];
   __shared__ float red[(S::THREADS + 63) / 64];
   __shared__ int is_last;
+  // Counted during the adjoint where one transform fills the workgroup, and
+  // its registers leave room for what that keeps alive (four per value do
+  // not: 16384 x 500 42.0 -> 44.2 us).
+  constexpr bool early = S::TPB == 1 && 512 / S::WPE > 4 * S::E;
   const int tid = threadIdx.x;
   const int slot = S::TPB == 1 ? 0 : tid / S::T;  // one transform: the row base is uniform
   const int t = tid - slot * S::T;
@@ -521,6 +572,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
     if ((tid & 63) == 0) red[tid >> 6] = acc;
   }
   transform_sync<S>();  // forward passes done with LDS; wave partials visible
+  float published = 0.f;
   if (t == 0 && live) {
     float total = acc;
     if constexpr (S::T > 64) {
@@ -530,17 +582,36 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
       for (int i = 0; i < S::T / 64; ++i) total += red[w0 + i];
     }
     if (total_out != nullptr)
-      atomicExch(&row_loss[row], total);  // published where every XCD sees it
+      published = fused_loss_publish<early>(&row_loss[row], total);
     else
       row_loss[row] = total;
   }
+  // Counted when the publication has completed by itself, before the
+  // gradient's stores, which the counters' round trips then do not wait for:
+  // during the adjoint or behind it.
+  const bool counts = total_out != nullptr && tid == 0;
+  CountProbe<2 * S::P - 2> probe{counters, gbase + blockIdx.x, counts, published};
   if (grad != nullptr) {  // uniform across the launch
-    run_passes<S, true>(a, lds, tw, t);
-    buffer_store_row<S>(a, Buf(grad + row0 * S::N), slot * S::N, t, live);
+    if constexpr (early)
+      run_passes<S, true>(a, lds, tw, t, &probe);
+    else
+      run_passes<S, true>(a, lds, tw, t);
   }
-  if (total_out != nullptr)  // uniform across the launch
-    fused_loss_total<S>(reinterpret_cast<float*>(lds_all), is_last, total_out, counters, row_loss_all,
-                        rows_all, groups_all, gbase + blockIdx.x);
+  if ((!early || grad == nullptr) && total_out != nullptr) {  // uniform across the launch
+    fused_loss_published<early>(published);
+    if constexpr (S::TPB > 1) __syncthreads();  // ... every slot's
+    if (tid == 0) probe.arrived = fused_loss_arrive(counters, gbase + blockIdx.x);
+  }
+  // With the answer in, the group's last goes on to the second level before
+  // its stores, behind which that round trip would wait.
+  if (early && counts) is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
+  if (grad != nullptr) buffer_store_row<S>(a, Buf(grad + row0 * S::N), slot * S::N, t, live);
+  if (total_out != nullptr) {
+    if (!early && tid == 0)
+      is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
+    __syncthreads();  // is_last visible; the LDS free for the sum's tree
+    if (is_last) fused_loss_sum<S>(reinterpret_cast<float*>(lds_all), total_out, row_loss_all, rows_all);
+  }
 }
 
 template <class S>
@@ -642,7 +713,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_stream(
           for (int i = 0; i < S::T / 64; ++i) total += red[i];
         }
         if (total_out != nullptr)
-          atomicExch(&row_loss[r], total);  // published where every XCD sees it
+          fused_loss_publish<false>(&row_loss[r], total);
         else
           row_loss[r] = total;
       }
@@ -655,9 +726,13 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_stream(
       __syncthreads();  // this row's exchange and partial reads are done before the next row's writes
     }
   }
-  if (total_out != nullptr)  // uniform across the launch
-    fused_loss_total<S>(reinterpret_cast<float*>(lds), is_last, total_out, counters, row_loss, rows,
-                        gridDim.x, blockIdx.x);
+  if (total_out != nullptr) {  // uniform across the launch
+    fused_loss_published<false>(0.f);  // the last row's, and so the others'
+    if (t == 0)
+      is_last = fused_loss_last(fused_loss_arrive(counters, blockIdx.x), counters, gridDim.x, blockIdx.x);
+    __syncthreads();  // is_last visible; the LDS free for the sum's tree
+    if (is_last) fused_loss_sum<S>(reinterpret_cast<float*>(lds), total_out, row_loss, rows);
+  }
 }
 
 template <class S>

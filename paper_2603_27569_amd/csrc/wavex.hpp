@@ -409,26 +409,25 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_wx(
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if ((tid & 63) == 0) red[tid >> 6] = acc;
   __syncthreads();  // forward passes done with the LDS; wave partials visible
+  float published = 0.f;
   if (tid == 0) {
     float total = 0.f;
 #pragma unroll
     for (int i = 0; i < S::THREADS / 64; ++i) total += red[i];
-    if (total_out != nullptr) {
-      // Published where every XCD sees it, then the workgroup counts itself
-      // at once, so the counters' round trips overlap the adjoint instead of
-      // waiting behind the gradient stores; this wave has nothing else in
-      // flight here.
-      atomicExch(&row_loss[row], total);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      is_last = fused_loss_count(counters, groups_all, gbase + blockIdx.x);
-    } else {
+    if (total_out != nullptr)
+      published = fused_loss_publish<true>(&row_loss[row], total);
+    else
       row_loss[row] = total;
-    }
   }
-  if (grad != nullptr) {  // uniform across the launch
-    wx_passes<S, true, NoProbe>(R, L, lds, nullptr);
-    wx_store<S, IoF32>(R, L, grad, row);
-  }
+  // Counted during the adjoint, as in k_spectral_energy.
+  const bool counts = total_out != nullptr && tid == 0;
+  CountProbe<4> probe{counters, gbase + blockIdx.x, counts, published};
+  if (grad != nullptr)  // uniform across the launch
+    wx_passes<S, true>(R, L, lds, &probe);
+  else
+    probe.mark(4);
+  if (counts) is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
+  if (grad != nullptr) wx_store<S, IoF32>(R, L, grad, row);
   if (total_out != nullptr) {  // uniform across the launch
     __syncthreads();  // is_last visible; the LDS free for the sum's tree
     if (is_last) fused_loss_sum<S>(reinterpret_cast<float*>(lds), total_out, row_loss_all, rows_all);
