@@ -32,7 +32,8 @@ int device_cus();
 // the 256 MiB Infinity Cache arrive faster through ordinary loads.  us on an
 // MI355X, hint / ordinary: ragged 2000 lengths (153 MB) 42.5 / 40.9 with the
 // rows cached, 41.1 / 42.7 with the rows in HBM; bfloat16 2048 x 3000 on the
-// matrix cores (49 MB) 12.7 / 12.2 and 14.2 / 14.6.  Beyond the cache the hint
+// matrix cores (49 MB) 12.7 / 12.2 and 14.2 / 14.6 (both measured before the
+// radix-32 ragged and the one-block matrix kernels, now 36.1 and 9.9).  Beyond the cache the hint
 // wins (4096 x 16384 in 16 bits: 3%), and at a few rows per CU the load phase
 // is one round trip, where it ties or wins (7% at 4096 x 256 from HBM).
 constexpr int64_t kStreamBelow = int64_t(24) << 20, kStreamAbove = int64_t(192) << 20;
