@@ -17,11 +17,12 @@
 // about 40% of that and overlaps with it as far as the resident workgroups
 // (16 waves per CU, limited by 128 VGPRs and 34 or 68 KiB of LDS) are in
 // different phases; at 2^20 x 16 the grid is two rounds of them, and the
-// stages take 55 + 51 us.  Against three radix-4 or radix-8 passes per stage
+// stages take 51 + 49 us.  Against three radix-4 or radix-8 passes per stage
 // and a closing transpose through LDS (the shape before) the two-pass columns
 // measure 36.1 against 45.7 us (2^16 x 101), 37.4 against 45.5 (2^15 x 200),
 // 76 against 91 (2^17 x 101), 81 against 94 (2^18 x 51), 104 against 118
-// (2^20 x 16), 28.8 against 37.9 (2^20 x 3) and 8.4 against 11.9 (2^16 x 1).
+// (2^20 x 16; 99.4 with the fused root butterflies), 28.8 against 37.9 (2^20 x
+// 3) and 8.4 against 11.9 (2^16 x 1).
 #pragma once
 
 #include "kernels.hpp"
