@@ -21,8 +21,8 @@
 // and a closing transpose through LDS (the shape before) the two-pass columns
 // measure 36.1 against 45.7 us (2^16 x 101), 37.4 against 45.5 (2^15 x 200),
 // 76 against 91 (2^17 x 101), 81 against 94 (2^18 x 51), 104 against 118
-// (2^20 x 16; 99.4 with the fused root butterflies), 28.8 against 37.9 (2^20 x
-// 3) and 8.4 against 11.9 (2^16 x 1).
+// (2^20 x 16; 100.5 with split-radix DFTs), 28.8 against 37.9 (2^20 x 3) and
+// 8.4 against 11.9 (2^16 x 1).
 #pragma once
 
 #include "kernels.hpp"
@@ -118,7 +118,7 @@ __device__ __forceinline__ void col_pass1(c32 (&a)[C::E]) {
     c32 v[C::R1];
 #pragma unroll
     for (int q = 0; q < C::R1; ++q) v[q] = a[b * C::R1 + q];
-    Dft<C::R1, INV, (C::E > 16)>::run(v);
+    Dft<C::R1, INV>::run(v);
 #pragma unroll
     for (int q = 0; q < C::R1; ++q) a[b * C::R1 + q] = v[q];
   }
@@ -146,11 +146,11 @@ __device__ __forceinline__ void col_stage1(const c32* src, c32* dst, const c32* 
     c32 p[C::R0];
 #pragma unroll
     for (int k = 1; k < C::R0; ++k) p[k] = as_c32(pb.ld64(8 * t, 8 * C::T * k));
-    Dft<C::R0, INV, (C::E > 16)>::run(a);
+    Dft<C::R0, INV>::run(a);
 #pragma unroll
     for (int k = 1; k < C::R0; ++k) a[k] = ctw<INV>(a[k], p[k]);
   } else {
-    Dft<C::R0, INV, (C::E > 16)>::run(a);
+    Dft<C::R0, INV>::run(a);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 1; k < C::R0; ++k) a[k] = ctw<INV>(a[k], as_c32(pb.ld64(8 * t, 8 * C::T * k)));
@@ -192,7 +192,7 @@ __device__ __forceinline__ void col_stage2(const c32* src, c32* dst, const c32* 
 #pragma unroll
     for (int m = 1; m < C::R0; ++m) a[m] = ctw<INV>(a[m], w[m]);
   }
-  Dft<C::R0, INV, (C::E > 16)>::run(a);
+  Dft<C::R0, INV>::run(a);
   {
     const c32 w0 = as_c32(Buf(atab + tile * C::THREADS).ld64(8 * tid, 0));
     const Buf pb(ptab);

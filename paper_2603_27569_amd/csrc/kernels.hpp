@@ -151,7 +151,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham(const c32* in, 
   c32* lds = lds_all + slot * S::LDS_ELEMS;
   c32 a[S::E];
   buffer_load_row<S>(a, Buf(in + row0 * S::N), slot_src<S>(slot, row, rows), t);
-  run_passes<ProductFirst<S>, INV>(a, lds, tw, t);
+  run_passes<S, INV>(a, lds, tw, t);
   buffer_store_row<S>(a, Buf(out + row0 * S::N), slot * S::N, t, live);
 }
 
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_four_step_columns(const 
   c32 a[S::E];
 #pragma unroll
   for (int m = 0; m < S::E; ++m) a[m] = src[(int64_t)(t + m * S::T) * N1];
-  run_passes<ProductFirst<S>, INV>(a, lds, tw, t);
+  run_passes<S, INV>(a, lds, tw, t);
   global_store_row<S, false>(a, y + (row * N1 + n1) * S::N, t, true);
 }
 

@@ -72,55 +72,51 @@ constexpr double cos_pi16(int k) {
 }
 constexpr double sin_pi16(int k) { return cos_pi16(k + 24); }
 
-// The radix-2 butterfly e + W o, e - W o with W = W_R^K = c + i s of the
-// direction, K < R / 2.  Exact roots take four additions.  FUSED: any other
-// root is its larger part times (1, t), |t| <= 1; two fused operations form
-// u = W o / c (or W o / s) and four add and subtract its multiple, six in all
-// where the product first (a multiplication and a fused operation per part)
-// and then the sums take eight, with as many roundings on the way to each
-// result.  A 16-point DFT is 148 operations instead of 168, a 32-point one 388
-// instead of 456.  |u| is at most sqrt(2) |W o|.
-//
-// The fused form is for kernels that the vector units bound (16-bit storage,
-// 42 operations per point and 4 + 4 bytes: binary16 4096 x 2048 14.45 -> 14.2
-// us, 16384 x 500 20.2 -> 18.9; 2000 ragged transforms 37.6 -> 36.3; the
-// two-transform kernels, matched filter 8192 x 300 16.7 -> 16.4).
-// Kernels that stream complex64 rows once keep the product first: memory
-// bounds them, and with the shorter bursts of work between its accesses the
-// chip moved 2 % less (16384 x 1024 52.2 -> 53.3 us, 65536 x 101 36.0 ->
-// 36.4).  Column kernels of 32 values per lane do more work per byte and gain
-// again (2^20 x 16 101.0 -> 100.0).
-template <int R, int K, bool INV, bool FUSED>
-__device__ __forceinline__ void root_butterfly(c32 e, c32 o, c32& plus, c32& minus) {
-  static_assert(32 % R == 0 && K >= 0 && 2 * K < R, "roots beyond W_32 are not tabulated");
+// v W_R^K of the direction.  Exact roots cost nothing; any other takes the
+// product first: a multiplication and a fused operation per part, no
+// intermediate of which exceeds |v|.  (Fusing the product with the sums that
+// follow, by scaling the root to (1, t), takes two operations fewer a pair but
+// passes through values of up to sqrt(2) |v|: rows within that factor of
+// FLT_MAX then came out infinite.)
+template <int R, int K, bool INV>
+__device__ __forceinline__ c32 mul_root(c32 v) {
+  static_assert(32 % R == 0 && K >= 0 && 4 * K <= 3 * R, "roots beyond W_32 are not tabulated");
   constexpr int k32 = K * 32 / R;
-  constexpr double c = cos_pi16(k32), s = INV ? sin_pi16(k32) : -sin_pi16(k32);
-  if constexpr (K != 0 && 4 * K != R && FUSED) {
-    constexpr bool by_c = c * c >= s * s;
-    constexpr float t = (float)(by_c ? s / c : c / s), f = (float)(by_c ? c : s);
-    const float ux = by_c ? __builtin_fmaf(-t, o.y, o.x) : __builtin_fmaf(t, o.x, -o.y);
-    const float uy = by_c ? __builtin_fmaf(t, o.x, o.y) : __builtin_fmaf(t, o.y, o.x);
-    plus = {__builtin_fmaf(f, ux, e.x), __builtin_fmaf(f, uy, e.y)};
-    minus = {__builtin_fmaf(-f, ux, e.x), __builtin_fmaf(-f, uy, e.y)};
+  if constexpr (K == 0) {
+    return v;
   } else {
-    constexpr float cf = (float)c, sf = (float)s;
-    const c32 w = K == 0 ? o : 4 * K == R ? mul_w4<INV>(o) : c32{cf * o.x - sf * o.y, cf * o.y + sf * o.x};
-    plus = cadd(e, w);
-    minus = csub(e, w);
+    constexpr float c = (float)cos_pi16(k32), s = (float)(INV ? sin_pi16(k32) : -sin_pi16(k32));
+    return {c * v.x - s * v.y, c * v.y + s * v.x};
   }
 }
 
 // ---------------------------------------------------------------- DFT_R
 // In-register length-R DFT, R in {2, 4, 8, 16, 32}, natural-order in and out,
-// by radix-2 decimation in time: DFT_R = combine(DFT_{R/2}(even),
-// W_R^k * DFT_{R/2}(odd)).  For R = 8 this is the split DIT butterfly of
-// Section V-B, eq. (4).
+// by split-radix decimation in time: with U = DFT_{R/2} of the even elements,
+// Z and Y = DFT_{R/4} of the elements 1 and 3 mod 4, z = W_R^k Z_k, y =
+// W_R^{3k} Y_k,
+//   X_k, X_{k + R/2}        = U_k         +- (z + y)
+//   X_{k + R/4}, X_{k + 3R/4} = U_{k + R/4} +- W_4 (z - y),
+// which for R = 4 is the radix-2 form.  Operations with every root applied
+// product first: 56 (R = 8), 160 (16), 424 (32), where radix-2 steps (for R =
+// 8 the split DIT butterfly of Section V-B, eq. (4)) take 56, 168 and 456:
+// 8 and 26 rotations instead of 10 and 34, and as many fewer roundings.  Against
+// radix-2 steps with the products fused into the sums (148 and 388 operations,
+// see mul_root) it measures, us on an MI355X: 4096 x 256 6.15 -> 6.04, 16384 x
+// 1024 52.0 -> 51.8, 65536 x 101 35.9 -> 36.0, 2^20 x 16 99.4 -> 100.5, matched
+// filter 8192 x 300 16.31 -> 16.30, binary16 4096 x 2048 14.34 -> 14.33, 2000
+// ragged transforms 36.3 -> 36.9.
 
-template <int R, bool INV, bool FUSED = true>
+template <int R, bool INV>
 struct Dft;
 
-template <bool INV, bool FUSED>
-struct Dft<2, INV, FUSED> {
+template <bool INV>
+struct Dft<1, INV> {
+  __device__ __forceinline__ static void run(c32 (&)[1]) {}
+};
+
+template <bool INV>
+struct Dft<2, INV> {
   __device__ __forceinline__ static void run(c32 (&v)[2]) {
     c32 a = v[0], b = v[1];
     v[0] = cadd(a, b);
@@ -128,26 +124,35 @@ struct Dft<2, INV, FUSED> {
   }
 };
 
-template <int R, bool INV, bool FUSED>
+template <int R, bool INV>
 struct Dft {
+  static constexpr int H = R / 2, Q = R / 4;
   template <int K>
-  __device__ __forceinline__ static void combine(c32 (&v)[R], const c32 (&e)[R / 2],
-                                                 const c32 (&o)[R / 2]) {
-    if constexpr (K < R / 2) {
-      root_butterfly<R, K, INV, FUSED>(e[K], o[K], v[K], v[K + R / 2]);
-      combine<K + 1>(v, e, o);
+  __device__ __forceinline__ static void combine(c32 (&v)[R], const c32 (&u)[H], const c32 (&z)[Q],
+                                                 const c32 (&y)[Q]) {
+    if constexpr (K < Q) {
+      const c32 zr = mul_root<R, K, INV>(z[K]), yr = mul_root<R, 3 * K, INV>(y[K]);
+      const c32 p = cadd(zr, yr), m = mul_w4<INV>(csub(zr, yr));
+      v[K] = cadd(u[K], p);
+      v[K + H] = csub(u[K], p);
+      v[K + Q] = cadd(u[K + Q], m);
+      v[K + H + Q] = csub(u[K + Q], m);
+      combine<K + 1>(v, u, z, y);
     }
   }
   __device__ __forceinline__ static void run(c32 (&v)[R]) {
-    c32 e[R / 2], o[R / 2];
+    c32 u[H], z[Q], y[Q];
 #pragma unroll
-    for (int i = 0; i < R / 2; ++i) {
-      e[i] = v[2 * i];
-      o[i] = v[2 * i + 1];
+    for (int i = 0; i < H; ++i) u[i] = v[2 * i];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      z[i] = v[4 * i + 1];
+      y[i] = v[4 * i + 3];
     }
-    Dft<R / 2, INV, FUSED>::run(e);
-    Dft<R / 2, INV, FUSED>::run(o);
-    combine<0>(v, e, o);
+    Dft<H, INV>::run(u);
+    Dft<Q, INV>::run(z);
+    Dft<Q, INV>::run(y);
+    combine<0>(v, u, z, y);
   }
 };
 
@@ -292,18 +297,6 @@ template <class S, class = void>
 struct double_buffered : std::false_type {};
 template <class S>
 struct double_buffered<S, std::void_t<decltype(S::DB)>> : std::integral_constant<bool, S::DB> {};
-
-// Kernels that stream complex64 rows run a shape's passes with products before
-// sums (see root_butterfly).
-template <class Base>
-struct ProductFirst : Base {
-  static constexpr bool PRODUCT_FIRST = true;
-};
-
-template <class S, class = void>
-struct product_first : std::false_type {};
-template <class S>
-struct product_first<S, std::void_t<decltype(S::PRODUCT_FIRST)>> : std::true_type {};
 
 // Split exchange: every exchange sends the real parts of the whole transform
 // through the LDS, then the imaginary parts: half the space like two rounds
@@ -560,7 +553,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
           for (int r = 1; r < R; ++r) v[r] = ctw<INV>(v[r], wb[r - 1]);
         }
       }
-      Dft<R, INV, !product_first<S>::value>::run(v);
+      Dft<R, INV>::run(v);
 #pragma unroll
       for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
     }
@@ -579,7 +572,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
     c32 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = a[b + r * BPT];
-    Dft<R, INV, !product_first<S>::value>::run(v);
+    Dft<R, INV>::run(v);
 #pragma unroll
     for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
   }

@@ -1,0 +1,89 @@
+"""Values near the largest float: an impulse z has bins of modulus |z|, so rows
+with |z| just below FLT_MAX have finite results and have to come out finite,
+whatever path takes them."""
+import numpy as np
+import pytest
+
+import paper_2603_27569_amd as sf
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+U = 2.0 ** -24
+Z = np.complex64(2.3e38 + 2.3e38j)  # |Z| = 0.956 FLT_MAX
+
+
+def _impulses(n):
+    """Rows with Z at every leg of the first pass and at scattered elements."""
+    gen = np.random.default_rng(n)
+    p = np.unique(np.concatenate([n // 32 * np.arange(32), gen.integers(0, n, 16)]))
+    x = np.zeros((len(p), n), dtype=np.complex64)
+    x[np.arange(len(p)), p] = Z
+    return p, x
+
+
+def _bins(p, n, inverse):
+    k = (p[:, None] * np.arange(n)[None, :]) % n
+    return complex(Z) * np.exp((2j if inverse else -2j) * np.pi * k / n)
+
+
+def _check(got, want, bound, what):
+    y = got.cpu().numpy().astype(np.complex128)
+    assert np.isfinite(y).all(), what
+    assert np.abs(y - want).max() <= bound * abs(complex(Z)), what
+
+
+# A bin is one root per radix-2 stage and one twiddle per pass, each off by a
+# few units: at most 6 U per stage and per pass of one transform.
+def _bound(n):
+    return 12 * U * np.log2(n)
+
+
+@pytest.mark.parametrize("inverse", [False, True], ids=["forward", "backward"])
+@pytest.mark.parametrize("n", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_single_pass(n, inverse):
+    p, x = _impulses(n)
+    want = _bins(p, n, inverse)
+    xt = torch.from_numpy(x).to(DEV)
+    direction = sf.FFT_BACKWARD if inverse else sf.FFT_FORWARD
+    _check(sf.fft(xt, inverse=inverse), want, _bound(n), "plain")
+    for v in sf.variants():
+        if v["n"] == n and v["kind"] == "single":
+            y = sf.fft(xt, inverse=inverse, algorithm=sf.FFT_ALGO_SINGLE_PASS, variant=v["name"])
+            _check(y, want, _bound(n), v["name"])
+    plan = sf.RaggedPlan([n] * len(x), direction)
+    _check(sf.ragged_fft(xt.reshape(-1), plan, graph=False).reshape(xt.shape), want, _bound(n), "ragged")
+    plan.close()
+    half = torch.view_as_real(xt).to(torch.bfloat16)
+    scale = float(half[0, 0, 0]) / Z.real  # Z as bfloat16 holds it
+    y = torch.view_as_complex(sf.fft_lowp(half, inverse=inverse).float().contiguous())
+    _check(y, scale * want, _bound(n) + 2.0 ** -8 * np.sqrt(2), "bfloat16")  # the result's rounding
+    sf.clear_plan_cache()
+
+
+@pytest.mark.parametrize("n", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_two_transforms(n):
+    p, x = _impulses(n)
+    xt = torch.from_numpy(x).to(DEV)
+    h = torch.ones(n, dtype=torch.complex64, device=DEV)
+    _check(sf.matched_filter(xt, h), x.astype(np.complex128), 2 * _bound(n), "filter")
+    # w^2 = 1 / 2n, so the gradient F^H(2 w^2 F x) is x again; the energies,
+    # |bin|^2, are beyond the range.
+    w = torch.full((n,), (2.0 * n) ** -0.5, dtype=torch.float32, device=DEV)
+    _, _, grad = sf.spectral_energy(xt, w)
+    _check(grad, x.astype(np.complex128), 2 * _bound(n) + 8 * U, "gradient")
+    sf.clear_plan_cache()
+
+
+@pytest.mark.parametrize("inverse", [False, True], ids=["forward", "backward"])
+@pytest.mark.parametrize("n", [1 << e for e in range(15, 21)])
+def test_four_step(n, inverse):
+    p, x = _impulses(n)
+    p, x = p[::7], x[::7]
+    want = _bins(p, n, inverse)
+    xt = torch.from_numpy(x).to(DEV)
+    for v in sf.variants():
+        if v["n"] == n and v["kind"] == "four_step":
+            y = sf.fft(xt, inverse=inverse, algorithm=sf.FFT_ALGO_FOUR_STEP, variant=v["name"])
+            _check(y, want, _bound(n), v["name"])
+    sf.clear_plan_cache()
