@@ -72,21 +72,36 @@ constexpr double cos_pi16(int k) {
 }
 constexpr double sin_pi16(int k) { return cos_pi16(k + 24); }
 
-// v W_R^K of the direction.  Exact roots cost nothing; any other takes the
-// product first: a multiplication and a fused operation per part, no
-// intermediate of which exceeds |v|.  (Fusing the product with the sums that
-// follow, by scaling the root to (1, t), takes two operations fewer a pair but
-// passes through values of up to sqrt(2) |v|: rows within that factor of
-// FLT_MAX then came out infinite.)
+// v W_R^K of the direction, W = c + i s.  Exact roots cost nothing; any other
+// takes two fused operations per part, product first: no intermediate exceeds
+// |v|.  (Fusing the product with the sums that follow, by scaling the root to
+// (1, t), takes two operations fewer a pair but passes through values of up to
+// sqrt(2) |v|: rows within that factor of FLT_MAX then came out infinite.)
+//
+// The larger of |c|, |s| is applied as a v = v + (a - 1) v: a - 1 is known 2 to
+// 50 times more closely in FP32 than a, whose rounding (half a unit at cos(pi /
+// 8) and cos(pi / 16)) would shift every output that passes the root the same
+// way.  rel-RMS errors with a and with a - 1: radix 16.32.32 at 16384 points
+// 1.33e-7 and 1.26e-7, 32 x 32 columns at 2^20 1.70e-7 and 1.55e-7.
 template <int R, int K, bool INV>
 __device__ __forceinline__ c32 mul_root(c32 v) {
   static_assert(32 % R == 0 && K >= 0 && 4 * K <= 3 * R, "roots beyond W_32 are not tabulated");
   constexpr int k32 = K * 32 / R;
+  constexpr double c = cos_pi16(k32), s = INV ? sin_pi16(k32) : -sin_pi16(k32);
   if constexpr (K == 0) {
     return v;
+  } else if constexpr (c * c >= s * s) {
+    // |c| v, then the other part; a negative c flips the whole
+    constexpr float a1 = (float)((c < 0 ? -c : c) - 1.0), b = (float)(c < 0 ? -s : s);
+    const c32 w{__builtin_fmaf(-b, v.y, __builtin_fmaf(a1, v.x, v.x)),
+                __builtin_fmaf(b, v.x, __builtin_fmaf(a1, v.y, v.y))};
+    return c < 0 ? c32{-w.x, -w.y} : w;
   } else {
-    constexpr float c = (float)cos_pi16(k32), s = (float)(INV ? sin_pi16(k32) : -sin_pi16(k32));
-    return {c * v.x - s * v.y, c * v.y + s * v.x};
+    // |s| v, then the other part, of W / i (or W / -i where s is negative)
+    constexpr float a1 = (float)((s < 0 ? -s : s) - 1.0), b = (float)(s < 0 ? c : -c);
+    const c32 w{__builtin_fmaf(-b, v.y, __builtin_fmaf(a1, v.x, v.x)),
+                __builtin_fmaf(b, v.x, __builtin_fmaf(a1, v.y, v.y))};
+    return s < 0 ? c32{w.y, -w.x} : c32{-w.y, w.x};
   }
 }
 
@@ -102,10 +117,10 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
 // 8 the split DIT butterfly of Section V-B, eq. (4)) take 56, 168 and 456:
 // 8 and 26 rotations instead of 10 and 34, and as many fewer roundings.  Against
 // radix-2 steps with the products fused into the sums (148 and 388 operations,
-// see mul_root) it measures, us on an MI355X: 4096 x 256 6.15 -> 6.04, 16384 x
-// 1024 52.0 -> 51.8, 65536 x 101 35.9 -> 36.0, 2^20 x 16 99.4 -> 100.5, matched
-// filter 8192 x 300 16.31 -> 16.30, binary16 4096 x 2048 14.34 -> 14.33, 2000
-// ragged transforms 36.3 -> 36.9.
+// see mul_root) it measures, us on an MI355X: 4096 x 256 5.85 -> 5.87, 16384 x
+// 1024 51.8 -> 51.7, 65536 x 101 35.9 -> 36.0, 2^20 x 16 99.7 -> 100.9, energy
+// 4096 x 512 11.7 -> 11.9, matched filter 8192 x 300 16.5 -> 16.7, binary16
+// 4096 x 2048 13.8 -> 13.8, 2000 ragged transforms 36.3 -> 37.2.
 
 template <int R, bool INV>
 struct Dft;
