@@ -21,7 +21,7 @@
 // and a closing transpose through LDS (the shape before) the two-pass columns
 // measure 36.1 against 45.7 us (2^16 x 101), 37.4 against 45.5 (2^15 x 200),
 // 76 against 91 (2^17 x 101), 81 against 94 (2^18 x 51), 104 against 118
-// (2^20 x 16; 100.9 with split-radix DFTs), 28.8 against 37.9 (2^20 x 3) and
+// (2^20 x 16; 101.0 with split-radix DFTs), 28.8 against 37.9 (2^20 x 3) and
 // 8.4 against 11.9 (2^16 x 1).
 #pragma once
 

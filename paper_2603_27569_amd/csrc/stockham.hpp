@@ -73,16 +73,19 @@ constexpr double cos_pi16(int k) {
 constexpr double sin_pi16(int k) { return cos_pi16(k + 24); }
 
 // v W_R^K of the direction, W = c + i s.  Exact roots cost nothing; any other
-// takes two fused operations per part, product first: no intermediate exceeds
-// |v|.  (Fusing the product with the sums that follow, by scaling the root to
-// (1, t), takes two operations fewer a pair but passes through values of up to
-// sqrt(2) |v|: rows within that factor of FLT_MAX then came out infinite.)
+// takes the product first, a multiplication and a fused operation per part: no
+// intermediate exceeds |v|.  (Fusing the product with the sums that follow, by
+// scaling the root to (1, t), takes two operations fewer a pair but passes
+// through values of up to sqrt(2) |v|: rows within that factor of FLT_MAX then
+// came out infinite.)
 //
-// The larger of |c|, |s| is applied as a v = v + (a - 1) v: a - 1 is known 2 to
-// 50 times more closely in FP32 than a, whose rounding (half a unit at cos(pi /
-// 8) and cos(pi / 16)) would shift every output that passes the root the same
-// way.  rel-RMS errors with a and with a - 1: radix 16.32.32 at 16384 points
-// 1.33e-7 and 1.26e-7, 32 x 32 columns at 2^20 1.70e-7 and 1.55e-7.
+// The rounding of a root's larger part shifts every value that passes the root
+// the same way.  For cos(pi / 8) and cos(pi / 16) it is half a unit, the most
+// there is: there a third operation adds what the rounding left out.  rel-RMS
+// errors without and with it: radix 16.32.32 at 16384 points 1.33e-7 and
+// 1.25e-7, 16.16.16 at 4096 1.22e-7 and 1.16e-7, 32 x 32 columns at 2^20 1.68e-7
+// and 1.55e-7; the radix-8 plans of 16384 and 4096 have 1.31e-7 and 1.21e-7.
+// (a v as v + (a - 1) v would cost nothing, but makes a NaN of an infinite v.)
 template <int R, int K, bool INV>
 __device__ __forceinline__ c32 mul_root(c32 v) {
   static_assert(32 % R == 0 && K >= 0 && 4 * K <= 3 * R, "roots beyond W_32 are not tabulated");
@@ -90,18 +93,17 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
   constexpr double c = cos_pi16(k32), s = INV ? sin_pi16(k32) : -sin_pi16(k32);
   if constexpr (K == 0) {
     return v;
-  } else if constexpr (c * c >= s * s) {
-    // |c| v, then the other part; a negative c flips the whole
-    constexpr float a1 = (float)((c < 0 ? -c : c) - 1.0), b = (float)(c < 0 ? -s : s);
-    const c32 w{__builtin_fmaf(-b, v.y, __builtin_fmaf(a1, v.x, v.x)),
-                __builtin_fmaf(b, v.x, __builtin_fmaf(a1, v.y, v.y))};
-    return c < 0 ? c32{-w.x, -w.y} : w;
   } else {
-    // |s| v, then the other part, of W / i (or W / -i where s is negative)
-    constexpr float a1 = (float)((s < 0 ? -s : s) - 1.0), b = (float)(s < 0 ? c : -c);
-    const c32 w{__builtin_fmaf(-b, v.y, __builtin_fmaf(a1, v.x, v.x)),
-                __builtin_fmaf(b, v.x, __builtin_fmaf(a1, v.y, v.y))};
-    return s < 0 ? c32{w.y, -w.x} : c32{-w.y, w.x};
+    constexpr bool by_c = c * c >= s * s;
+    constexpr double a = by_c ? c : s, b = by_c ? s : c;  // |a| >= |b|
+    constexpr float ah = (float)a, al = (float)(a - (double)ah), bf = (float)b;
+    constexpr bool close = a * a > 0.75;  // +-cos(pi / 8), +-cos(pi / 16)
+    const auto part = [](float big, float small) {  // a big + b small
+      float r = bf * small;
+      if constexpr (close) r = __builtin_fmaf(al, big, r);
+      return __builtin_fmaf(ah, big, r);
+    };
+    return by_c ? c32{part(v.x, -v.y), part(v.y, v.x)} : c32{part(-v.y, v.x), part(v.x, v.y)};
   }
 }
 
@@ -112,15 +114,15 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
 // W_R^{3k} Y_k,
 //   X_k, X_{k + R/2}        = U_k         +- (z + y)
 //   X_{k + R/4}, X_{k + 3R/4} = U_{k + R/4} +- W_4 (z - y),
-// which for R = 4 is the radix-2 form.  Operations with every root applied
-// product first: 56 (R = 8), 160 (16), 424 (32), where radix-2 steps (for R =
-// 8 the split DIT butterfly of Section V-B, eq. (4)) take 56, 168 and 456:
-// 8 and 26 rotations instead of 10 and 34, and as many fewer roundings.  Against
-// radix-2 steps with the products fused into the sums (148 and 388 operations,
-// see mul_root) it measures, us on an MI355X: 4096 x 256 5.85 -> 5.87, 16384 x
-// 1024 51.8 -> 51.7, 65536 x 101 35.9 -> 36.0, 2^20 x 16 99.7 -> 100.9, energy
-// 4096 x 512 11.7 -> 11.9, matched filter 8192 x 300 16.5 -> 16.7, binary16
-// 4096 x 2048 13.8 -> 13.8, 2000 ragged transforms 36.3 -> 37.2.
+// which for R = 4 is the radix-2 form.  There are 2, 8 and 26 rotations (R = 8,
+// 16, 32) where radix-2 steps (for R = 8 the split DIT butterfly of Section V-B,
+// eq. (4)) have 2, 10 and 34, and as many fewer roundings; 56, 168 and 448
+// operations with mul_root's.  Against radix-2 steps with the products fused
+// into the sums (52, 148 and 388 operations, but see mul_root) it measures, us
+// on an MI355X: 4096 x 256 5.91 -> 5.87, 16384 x 1024 51.9 -> 52.3, 65536 x 101
+// 36.0 -> 36.0, 2^20 x 16 99.4 -> 101.0, energy 4096 x 512 11.8 -> 11.9, matched
+// filter 8192 x 300 16.4 -> 16.7, binary16 4096 x 2048 13.6 -> 13.6, 2000 ragged
+// transforms 36.2 -> 37.1.
 
 template <int R, bool INV>
 struct Dft;

@@ -87,3 +87,28 @@ def test_four_step(n, inverse):
             y = sf.fft(xt, inverse=inverse, algorithm=sf.FFT_ALGO_FOUR_STEP, variant=v["name"])
             _check(y, want, _bound(n), v["name"])
     sf.clear_plan_cache()
+
+
+@pytest.mark.parametrize("inverse", [False, True], ids=["forward", "backward"])
+@pytest.mark.parametrize("n", [256, 512, 1024, 2048, 4096, 8192, 16384])
+def test_infinite_value(n, inverse):
+    """An infinite leg of the first pass gives bins of infinite parts, signed as
+    the roots are, and no NaN: it meets no twiddle, and its root does not turn it
+    into a difference of infinities."""
+    sign = 1 if inverse else -1
+    for v in sf.variants():
+        r = v["radices"][0] if v["kind"] == "single" and v["n"] == n else 0
+        if r < 8:
+            continue
+        legs = np.array([k for k in (1, 2, 3, 4, 6, 12) if k < r])  # one root each on the way to any bin
+        x = np.zeros((len(legs), n), dtype=np.complex64)
+        x[np.arange(len(legs)), n // r * legs] = np.inf
+        y = sf.fft(torch.from_numpy(x).to(DEV), inverse=inverse, algorithm=sf.FFT_ALGO_SINGLE_PASS,
+                   variant=v["name"]).cpu().numpy()
+        assert not np.isnan(y.view(np.float32)).any(), v["name"]
+        quarter = (4 * legs[:, None] * np.arange(n)[None, :]) // r % 4  # quadrant of the root
+        part = (4 * legs[:, None] * np.arange(n)[None, :]) % r != 0  # neither part of the root is zero
+        re = np.where(np.isin(quarter, (0, 3)), np.inf, -np.inf)
+        im = sign * np.where(quarter < 2, np.inf, -np.inf)
+        assert np.array_equal(y.real[part], re[part]) and np.array_equal(y.imag[part], im[part]), v["name"]
+    sf.clear_plan_cache()
