@@ -307,9 +307,11 @@ def cached_plan(n, batch, direction, device_index, algorithm=FFT_ALGO_AUTO, vari
 
 def clear_plan_cache():
     with _cache_lock:
-        for p in _plan_cache.values():
-            p.close()
+        # out of the cache first: _plan_for reads it without the lock
+        plans = list(_plan_cache.values())
         _plan_cache.clear()
+        for p in plans:
+            p.close()
 
 
 # ------------------------------------------------------------ torch helpers
