@@ -375,7 +375,10 @@ int fft_set_launch_limit(int64_t max_groups);
  *   single-pass variant "variant_resources" (VGPRs, scratch bytes per lane,
  *   static LDS bytes and the largest workgroup of its forward FP32 kernel,
  *   as the HIP runtime reports them for the plan's device), the matched-
- *   filter, fused and 16-bit storage shapes.  Errors: FFT_INVALID_PLAN, or
+ *   filter, fused and 16-bit storage shapes.  A column split's "variant" has
+ *   kind "columns", the radices of its two kernels and the entries of their
+ *   tables; "variant_resources" are the first kernel's, "second_resources"
+ *   the second's.  Errors: FFT_INVALID_PLAN, or
  *   FFT_INVALID_ARGUMENT for a buffer that is too small.
  */
 int fft_variant_count(void);

@@ -736,7 +736,8 @@ static void log_plan(const stockfft_plan_s* p, bool named) {
                "stockfft: plan n=%lld batch=%lld direction=%d algorithm=%s variant=%s "
                "four_step=%s fused=%s filter=%s storage16=%s source=%s\n",
                (long long)p->n, (long long)p->batch, p->direction,
-               p->algorithm == FFT_ALGO_FOUR_STEP ? "four_step" : "single_pass", nm(p->sv),
+               p->algorithm == FFT_ALGO_FOUR_STEP ? "four_step" : "single_pass",
+               nm(p->fs && p->fs->column() ? nullptr : p->sv),
                p->fs ? p->fs->name : "-", nm(p->sv_fused), nm(p->sv_filter), nm(p->sv_storage16),
                named ? "named" : "tuned");
 }
@@ -1241,17 +1242,37 @@ extern "C" int fft_variant_twiddles(int index, float* out, int64_t cap_complex, 
   return FFT_SUCCESS;
 }
 
-// The compiled resources of a variant's forward FP32 kernel on the plan's
-// device: registers, scratch and static LDS per the HIP runtime.
-static std::string kernel_resources(const stockfft_plan_s* plan, const SingleVariant& v) {
-  if (!v.kernel) return "";
+// The compiled resources of a forward FP32 kernel on the plan's device:
+// registers, scratch and static LDS per the HIP runtime, as the member `key`.
+static std::string kernel_resources(const stockfft_plan_s* plan, const char* key, const void* kernel) {
+  if (!kernel) return "";
   DeviceGuard g(plan->device);
   hipFuncAttributes a{};
-  if (hipFuncGetAttributes(&a, v.kernel) != hipSuccess) return "";
-  return ",\"variant_resources\":{\"vgprs\":" + std::to_string(a.numRegs) +
+  if (hipFuncGetAttributes(&a, kernel) != hipSuccess) return "";
+  return ",\"" + std::string(key) + "\":{\"vgprs\":" + std::to_string(a.numRegs) +
          ",\"scratch_bytes_per_lane\":" + std::to_string(a.localSizeBytes) +
          ",\"lds_bytes\":" + std::to_string(a.sharedSizeBytes) +
          ",\"max_threads\":" + std::to_string(a.maxThreadsPerBlock) + "}";
+}
+
+// What a column split's plan runs: the two register passes of each stage and
+// the entries of its tables on the device.
+static std::string describe_columns(const FourStepVariant& f) {
+  const ColumnShape& c = f.column_shape;
+  const auto pair = [](int a, int b) { return "[" + std::to_string(a) + "," + std::to_string(b) + "]"; };
+  return "{\"kind\":\"columns\",\"name\":\"" + std::string(f.name) + "\",\"n\":" + std::to_string(f.n) +
+         ",\"first_radices\":" + pair(c.r0_first, c.r1_first) + ",\"second_radices\":" +
+         pair(c.r0_second, c.r1_second) + ",\"twiddle_entries\":" +
+         std::to_string(column_twiddle_entries(c)) + "}";
+}
+
+// The kernels a plan's transform runs.
+static std::string describe_kernels(const stockfft_plan_s* plan) {
+  const FourStepVariant* f = plan->fs;
+  if (f && f->column())
+    return describe_columns(*f) + kernel_resources(plan, "variant_resources", f->first_kernel) +
+           kernel_resources(plan, "second_resources", f->second_kernel);
+  return describe_single(*plan->sv) + kernel_resources(plan, "variant_resources", plan->sv->kernel);
 }
 
 extern "C" int fft_plan_describe(fft_plan_t plan, char* buf, int64_t cap) {
@@ -1262,7 +1283,7 @@ extern "C" int fft_plan_describe(fft_plan_t plan, char* buf, int64_t cap) {
                   ",\"algorithm\":\"" +
                   (plan->algorithm == FFT_ALGO_FOUR_STEP ? "four_step" : "single_pass") + "\"" +
                   ",\"workspace_bytes\":" + std::to_string(plan->ws_bytes) +
-                  ",\"variant\":" + describe_single(*plan->sv) + kernel_resources(plan, *plan->sv) +
+                  ",\"variant\":" + describe_kernels(plan) +
                   (plan->fs ? ",\"four_step\":" + describe_four_step(*plan->fs) : "") +
                   (plan->sv_filter ? ",\"filter_variant\":\"" + std::string(plan->sv_filter->name) + "\""
                                    : "") +

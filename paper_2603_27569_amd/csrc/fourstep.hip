@@ -27,7 +27,9 @@ template <class First, class Second>
 FourStepVariant column_variant(const char* name, const char* sub_name, int tw_sub_elems, const char* sub2_name) {
   using S = Split<First, Second>;
   return {name, (int)S::N, S::N1, S::N2, sub_name, tw_sub_elems, &launch_columns_first<S>,
-          &launch_columns_second<S>, true, sub2_name, S::shape};
+          &launch_columns_second<S>, true, sub2_name, S::shape,
+          reinterpret_cast<const void*>(&k_columns_first<S, false, 0>),
+          reinterpret_cast<const void*>(&k_columns_second<S, false, 0>)};
 }
 constexpr const char* kSub256 = "n256_e4_b4_p4_r4.4.4.4";
 constexpr const char* kSub512 = "n512_e8_b4_p4_r8.8.8";

@@ -101,6 +101,10 @@ inline void four_step_twiddles(int64_t n1, int64_t n2, bool two_level, std::vect
 struct ColumnShape {
   int r0_first, r1_first, r0_second, r1_second, tile_second;
 };
+inline int64_t column_twiddle_entries(const ColumnShape& c) {
+  const int64_t n2 = (int64_t)c.r0_first * c.r1_first, n1 = (int64_t)c.r0_second * c.r1_second;
+  return n2 + n1 + n2 * (c.r0_second + c.r1_second);
+}
 inline void column_twiddles(const ColumnShape& c, std::vector<float>& out) {
   const int64_t n2 = (int64_t)c.r0_first * c.r1_first, n1 = (int64_t)c.r0_second * c.r1_second;
   const int64_t N = n1 * n2;

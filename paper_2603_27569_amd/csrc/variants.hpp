@@ -113,6 +113,8 @@ struct FourStepVariant {
   // sub shapes then only describe the roots of the split.
   const char* sub2_name;  // N1-point shape of splits with N1 != N2 (or null)
   ColumnShape column_shape;
+  const void* first_kernel;   // a column split's forward kernels, for resource
+  const void* second_kernel;  // queries (hipFuncGetAttributes)
   bool column() const { return column_shape.tile_second > 0; }
 };
 
