@@ -295,11 +295,20 @@ k_stockham_mma(const uint32_t* in, uint32_t* out, const c32* __restrict__ tw, in
   }
 }
 
+// Loads (stream_rows).  Up to 64 MiB in and out the launch is one generation of
+// waves and the hint is faster or level wherever the rows are; above 192 MiB
+// the cache holds no part worth having.  us on an MI355X, rows from HBM / just
+// written, hint against ordinary: 4096 x 1050 9.7 / 9.0 against 10.0 / 9.3, 4096
+// x 2048 14.6 / 13.8 against 15.4 / 13.9, 4096 x 2500 21.5 / 20.2 against 22.1 /
+// 16.5, 2048 x 8000 31.9 / 30.6 against 32.7 / 24.1, 4096 x 6000 45.5 / 44.4
+// against 46.2 / 45.9.
+constexpr int64_t kOrdinaryFrom = int64_t(64) << 20, kOrdinaryTo = int64_t(192) << 20;
+
 template <int N, int THREADS, class IO, int TPWG = 1>
 hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t batch,
                               bool inverse, hipStream_t s) {
   const int64_t cap = max_groups_per_launch() * TPWG;  // rows per launch
-  const int stream = stream_rows(2 * batch * N * (int64_t)sizeof(uint32_t));
+  const int stream = stream_rows(2 * batch * N * (int64_t)sizeof(uint32_t), kOrdinaryFrom, kOrdinaryTo);
   for (int64_t r0 = 0; r0 < batch; r0 += cap) {
     const int64_t rows = batch - r0 < cap ? batch - r0 : cap;
     const uint32_t* ip = static_cast<const uint32_t*>(in) + r0 * N;

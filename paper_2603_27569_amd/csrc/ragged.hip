@@ -251,6 +251,14 @@ int shape_index(const char* name) {
   return -1;
 }
 
+// Loads (stream_rows): us on an MI355X, rows from HBM / just written, hint
+// against ordinary: 700 lengths (51 MiB) 17.2 / 16.3 against 18.3 / 17.0, 1200
+// (88) 24.6 / 23.6 against 27.0 / 23.4, 1500 (109) 26.9 / 25.3 against 30.2 /
+// 25.4, 1700 (123) 31.7 / 30.6 against 35.0 / 29.0, 2000 (146) 36.9 / 34.7 against
+// 39.2 / 32.8, 2200 (158) 41.5 / 40.5 against 43.9 / 35.1, 2600 (187) 48.5 / 47.1
+// against 51.3 / 48.9.
+constexpr int64_t kOrdinaryFrom = int64_t(128) << 20, kOrdinaryTo = int64_t(160) << 20;
+
 // Built-in per-length shape: the autotuner's choice on MI355X (the package's
 // tune_gfx950.json).
 constexpr int kBuiltinShape[kClasses] = {0, 2, 4, 6, 9, 10, 12};
@@ -454,7 +462,7 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
   p->args.tasks = p->d_tasks;
   p->args.item_off = p->d_off;
   p->args.wg_cls = p->d_wg;
-  p->args.stream = stream_rows(2 * total * (int64_t)sizeof(c32));
+  p->args.stream = stream_rows(2 * total * (int64_t)sizeof(c32), kOrdinaryFrom, kOrdinaryTo);
 
   for (int c = 0; c < kClasses; ++c) p->args.tw[c] = static_cast<const c32*>(p->d_tw[c]);
   register_handle(p);

@@ -29,15 +29,11 @@ int device_cus();
 // Whether a launch that moves `bytes` of rows in and out should load its rows
 // with the streaming hint (ragged batches and the matrix-core transform).  The
 // hint keeps rows that come from HBM out of the caches; rows that are still in
-// the 256 MiB Infinity Cache arrive faster through ordinary loads.  us on an
-// MI355X, hint / ordinary: ragged 2000 lengths (153 MB) 42.5 / 40.9 with the
-// rows cached, 41.1 / 42.7 with the rows in HBM; bfloat16 2048 x 3000 on the
-// matrix cores (49 MB) 12.7 / 12.2 and 14.2 / 14.6 (both measured before the
-// radix-32 ragged and the one-block matrix kernels, now 36.1 and 9.9).  Beyond the cache the hint
-// wins (4096 x 16384 in 16 bits: 3%), and at a few rows per CU the load phase
-// is one round trip, where it ties or wins (7% at 4096 x 256 from HBM).
-constexpr int64_t kStreamBelow = int64_t(24) << 20, kStreamAbove = int64_t(192) << 20;
-inline bool stream_rows(int64_t bytes) { return bytes < kStreamBelow || bytes > kStreamAbove; }
+// the 256 MiB Infinity Cache arrive faster through ordinary loads.  Where a
+// caller's rows are is not known here, so ordinary loads are taken in the
+// range (from, to] only, where they gain at least as much on cached rows as
+// they lose on rows from HBM; each caller states its range and both sides.
+inline bool stream_rows(int64_t bytes, int64_t from, int64_t to) { return bytes <= from || bytes > to; }
 
 using LaunchFn = hipError_t (*)(const void* in, void* out, const void* tw, int64_t batch,
                                 bool inverse, hipStream_t s);
