@@ -26,6 +26,8 @@
 // parts in accumulators 0 .. 7 and imaginary parts in 8 .. 15.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.hpp"
 #include "kernels.hpp"
 
@@ -152,6 +154,15 @@ __device__ __forceinline__ void next_twiddles(c32 (&wn)[8], const char* table, i
   for (int q = 0; q < 8; ++q) wn[q] = r > 0 ? wn[q] : c32{1.f, 0.f};
 }
 
+// a w, or a conj(w) for the backward transform, with its fused operations spelled
+// out: left to the compiler they come out differently with four blocks per
+// wave, and the bits of a row would depend on the size of its batch.
+template <bool INV>
+__device__ __forceinline__ c32 twiddled(c32 a, c32 w) {
+  if constexpr (INV) return {__builtin_fmaf(a.x, w.x, a.y * w.y), __builtin_fmaf(a.y, w.x, -(a.x * w.y))};
+  else return {__builtin_fmaf(a.x, w.x, -(a.y * w.y)), __builtin_fmaf(a.x, w.y, a.y * w.x)};
+}
+
 // Waves per SIMD to leave registers for.  Two blocks' products and twiddles
 // fit the 64 registers of 8 waves when the blocks go one after the other
 // (512's unrolled radix-2 pass needs a few more), four together those of 4.
@@ -255,7 +266,7 @@ k_stockham_mma(const uint32_t* in, uint32_t* out, const c32* __restrict__ tw, in
                          step * 4 * h;
 #pragma unroll
           for (int q = 0; q < 8; ++q)
-            wr[step * (q + (q & 4))] = IO::store(ctw<INV>(c32{acc[g][q], acc[g][8 + q]}, wn[g][q]));
+            wr[step * (q + (q & 4))] = IO::store(twiddled<INV>(c32{acc[g][q], acc[g][8 + q]}, wn[g][q]));
         }
       }
     }
@@ -295,14 +306,15 @@ k_stockham_mma(const uint32_t* in, uint32_t* out, const c32* __restrict__ tw, in
   }
 }
 
-// Loads (stream_rows).  Up to 64 MiB in and out the launch is one generation of
-// waves and the hint is faster or level wherever the rows are; above 192 MiB
-// the cache holds no part worth having.  us on an MI355X, rows from HBM / just
-// written, hint against ordinary: 4096 x 1050 9.7 / 9.0 against 10.0 / 9.3, 4096
-// x 2048 14.6 / 13.8 against 15.4 / 13.9, 4096 x 2500 21.5 / 20.2 against 22.1 /
-// 16.5, 2048 x 8000 31.9 / 30.6 against 32.7 / 24.1, 4096 x 6000 45.5 / 44.4
-// against 46.2 / 45.9.
-constexpr int64_t kOrdinaryFrom = int64_t(64) << 20, kOrdinaryTo = int64_t(192) << 20;
+// Loads (stream_rows).  Up to 44 MiB in and out, two thirds of a generation of
+// waves, the hint is faster or level wherever the rows are; above 192 MiB the
+// cache holds no part worth having.  us on an MI355X, rows from HBM / just
+// written, hint against ordinary: 4096 x 1050 9.7 / 9.0 against 10.0 / 9.3, 2048
+// x 2500 10.5 / 9.8 against 11.0 / 10.0, bfloat16 2048 x 3000 12.9 / 11.9 against
+// 13.4 / 10.2, 4096 x 2048 14.6 / 13.8 against 15.4 / 13.9, 4096 x 2500 21.5 /
+// 20.2 against 22.1 / 16.5, 2048 x 8000 31.9 / 30.6 against 32.7 / 24.1, 4096 x
+// 6000 45.5 / 44.4 against 46.2 / 45.9.
+constexpr int64_t kOrdinaryFrom = int64_t(44) << 20, kOrdinaryTo = int64_t(192) << 20;
 
 template <int N, int THREADS, class IO, int TPWG = 1>
 hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t batch,
@@ -331,21 +343,26 @@ hipError_t launch_mma_threads(const void* in, void* out, const void* tw, int64_t
 //   4.9 / 5.4, 4096 x 257 4.6 / 4.8 / 5.8, 8192 x 129 6.5 / 6.8 / 7.6;
 //   beyond, two blocks share the matrix operands and leave fewer waves to
 //   start: 512 x 6145 7.2 / 6.7 / 8.1, 2048 x 4097 16.4 / 15.6 / 16.8, 8192 x
-//   3201 69.6 / 67.5 / 70.7 (with the input in HBM 2048 x 1537 takes 8.9 / 8.3
-//   / 8.5);
+//   3201 69.6 / 67.5 / 70.7;
 //   512 and 1024 gain from whole transforms per wave once all waves are full
-//   (1024 x 8193 15.9 / 15.7 / 14.2, x 25601 51.6 / 52.1 / 46.3); the other
-//   lengths do not.
+//   (1024 x 8193 15.9 / 15.7 / 14.2, x 25601 51.6 / 52.1 / 46.3); at 2048 and
+//   4096 four blocks keep a launch of 12 to 16 blocks per SIMD in one generation
+//   of half the waves (2 / 4 per wave, rows from HBM, then just written): 4096 x
+//   1500 12.3 / 12.3, 10.6 / 11.6, x 1625 15.9 / 13.0, 11.9 / 12.2, x 2048 18.9 /
+//   15.4, 13.6 / 13.8, x 2500 22.1 / 24.2, 16.5 / 18.1; 2048 x 3500 17.5 / 14.0,
+//   12.2 / 12.7.  bfloat16, whose rounding takes more operations, gains at 4096
+//   (x 2048 18.1 / 16.6, 13.5 / 13.1) but not at 2048 (x 3250 15.8 / 13.4, 10.7 /
+//   12.4); 8192 does not gain (x 1024 19.0 / 19.1, 18.1 / 18.2).
 // 16384 has no one-block form (2048 lanes).  The kernel before this one (four
 // blocks, 102 ... 168 registers, 64-bit addresses and the matrix formed in
 // registers) took 6.9 at 512 x 129, 5.6 at 2048 x 513, 5.2 at 4096 x 257, 7.9 at
-// 8192 x 129, 11.7 at 512 x 6145, 19.4 at 2048 x 4097, 19.6 at 1024 x 8193 and
-// 93.2 at 16384 x 1601 (now 70.5).
+// 8192 x 129, 11.7 at 512 x 6145, 19.4 at 2048 x 4097, 19.6 at 1024 x 8193, 17.6
+// at 4096 x 2048 and 93.2 at 16384 x 1601 (now 70.5).
 template <class IO>
 hipError_t launch_mma(int64_t n, const void* in, void* out, const void* tw, int64_t batch,
                       bool inverse, hipStream_t s) {
   const int64_t blocks = batch * (n / 512);
-  const bool one = blocks <= 4096, four = blocks > 8192;
+  const bool one = blocks <= 4096, four = n <= 1024 ? blocks > 8192 : blocks > 12288 && blocks <= 16384;
   switch (n) {
     case 512:
       if (one) return launch_mma_threads<512, 64, IO, 1>(in, out, tw, batch, inverse, s);
@@ -357,9 +374,12 @@ hipError_t launch_mma(int64_t n, const void* in, void* out, const void* tw, int6
       return launch_mma_threads<1024, 64, IO, 2>(in, out, tw, batch, inverse, s);
     case 2048:
       if (one) return launch_mma_threads<2048, 256, IO>(in, out, tw, batch, inverse, s);
+      if constexpr (std::is_same<IO, IoF16>::value)
+        if (four) return launch_mma_threads<2048, 64, IO>(in, out, tw, batch, inverse, s);
       return launch_mma_threads<2048, 128, IO>(in, out, tw, batch, inverse, s);
     case 4096:
       if (one) return launch_mma_threads<4096, 512, IO>(in, out, tw, batch, inverse, s);
+      if (four) return launch_mma_threads<4096, 128, IO>(in, out, tw, batch, inverse, s);
       return launch_mma_threads<4096, 256, IO>(in, out, tw, batch, inverse, s);
     case 8192:
       if (one) return launch_mma_threads<8192, 1024, IO>(in, out, tw, batch, inverse, s);

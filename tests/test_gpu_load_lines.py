@@ -12,7 +12,7 @@ MIB = 1 << 20
 
 
 @pytest.mark.parametrize("n", [512, 4096, 16384])
-@pytest.mark.parametrize("edge", [64 * MIB, 192 * MIB])
+@pytest.mark.parametrize("edge", [44 * MIB, 192 * MIB])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_matrix_core(n, edge, dtype):
     batch = edge // (8 * n)
