@@ -282,7 +282,9 @@ int fft_destroy_ragged(fft_ragged_plan_t plan);
  * per task, hence the LDS tile); the autotuner picks one per size.
  * fft_ragged_shapes: comma-separated shape names for length n, into buf.
  * fft_tune_set_ragged: use `shape` for length n in ragged plans made later.
- * fft_tune_query_ragged: the shape ragged plans would use for n, into buf.
+ * fft_tune_query_ragged: the shape ragged plans would use for n, into buf
+ *   (without a shape set for n = 8192 a plan takes the length's other shape
+ *   where it predicts that its batch finishes earlier with it).
  * fft_tune_clear_ragged: back to the built-in shapes (the tuned MI355X choice).
  * Host only.  Errors: FFT_INVALID_POINTER, FFT_INVALID_SIZE,
  * FFT_INVALID_ARGUMENT (unknown shape, shape for another length, small buffer).

@@ -21,11 +21,15 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <functional>
+#include <iterator>
 #include <mutex>
 #include <new>
 #include <queue>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/stockfft.h"
@@ -280,7 +284,7 @@ struct stockfft_ragged_s {
   int ntasks = 0;
   int grid = 0;
   int shape_of_class[kClasses] = {};
-  int64_t class_count[7] = {};
+  int64_t class_count[kClasses] = {};
   Task* d_tasks = nullptr;
   int64_t* d_off = nullptr;
   int* d_wg = nullptr;
@@ -315,6 +319,58 @@ static SingleVariant as_variant(const ShapeInfo& s) {
   return v;
 }
 
+// The tasks of a plan and their workgroups.
+struct Layout {
+  std::vector<Task> tasks;
+  std::vector<int> owner;  // of each task
+  int grid = 0;
+  double finish = 0;  // predicted, in the unit of kShapeTaskUs
+};
+
+// Tasks of class_count[c] transforms of each class in the given shapes, largest
+// class first (the order of the offsets), and their list schedule (Graham's
+// longest-processing-time rule): tasks, longest length first, each go to the
+// workgroup with the least work so far.  A task costs its shape's measured
+// duration, scaled down for a partly filled task: half of it (the loads and
+// stores) is taken as proportional to the live transforms, the other half (the
+// arithmetic of every slot) not.  Two workgroups share a CU (w and w + cus);
+// once one is done the other runs twice as fast.
+static Layout lay_out(const int64_t (&class_count)[kClasses], const int (&shape_of_class)[kClasses], int cus) {
+  Layout l;
+  std::vector<double> cost;
+  int64_t first = 0;
+  for (int c = kClasses - 1; c >= 0; --c) {
+    const int shape = shape_of_class[c], tpb = kShapes[shape].tpb;
+    for (int64_t j = 0; j < class_count[c]; j += tpb) {
+      const int n = (int)std::min<int64_t>(tpb, class_count[c] - j);
+      l.tasks.push_back(Task{first + j, n, c});
+      cost.push_back(kShapeTaskUs[shape] * (0.5 + 0.5 * n / tpb));
+    }
+    first += class_count[c];
+  }
+  l.grid = std::max(1, std::min(2 * cus, (int)l.tasks.size()));  // two workgroups per CU
+  std::vector<size_t> order(l.tasks.size());
+  for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+  using Load = std::pair<double, int>;
+  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
+  std::vector<double> load(2 * cus, 0.0);
+  for (int w = 0; w < l.grid; ++w) heap.push(Load{0, w});
+  l.owner.resize(l.tasks.size());
+  for (size_t i : order) {
+    const int w = heap.top().second;
+    heap.pop();
+    l.owner[i] = w;
+    load[w] += cost[i];
+    heap.push(Load{load[w], w});
+  }
+  for (int w = 0; w < cus; ++w) {
+    const double a = load[w], b = load[w + cus];
+    l.finish = std::max(l.finish, std::min(a, b) + 0.5 * std::fabs(a - b));
+  }
+  return l;
+}
+
 extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, int64_t count,
                                int direction) {
   if (!plan) return FFT_INVALID_POINTER;
@@ -337,10 +393,13 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
   p->device = dev;
   p->count = count;
   p->total = total;
+  bool named[kClasses];
   {
     std::lock_guard<std::mutex> lk(g_rtune_mu);
-    for (int c = 0; c < 7; ++c)
-      p->shape_of_class[c] = g_rtune[c] >= 0 ? g_rtune[c] : builtin_shape(int64_t(256) << c);
+    for (int c = 0; c < kClasses; ++c) {
+      named[c] = g_rtune[c] >= 0;
+      p->shape_of_class[c] = named[c] ? g_rtune[c] : builtin_shape(int64_t(256) << c);
+    }
   }
 
   // Offsets in the packed buffer, grouped by size class, largest class first
@@ -354,22 +413,13 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
     }
   }
   std::vector<int64_t> item_off;
-  std::vector<Task> tasks;
   item_off.reserve(count);
-  for (int c = 6; c >= 0; --c) {
-    const int64_t n = int64_t(256) << c;
-    const int shape = p->shape_of_class[c];
-    const int tpb = kShapes[shape].tpb;
-    const int64_t first = (int64_t)item_off.size();
+  for (int c = kClasses - 1; c >= 0; --c) {
+    const int64_t n = int64_t(256) << c, first = (int64_t)item_off.size();
     for (int64_t i = 0; i < count; ++i)
       if (sizes[i] == n) item_off.push_back(offs[i]);
-    const int64_t k = (int64_t)item_off.size() - first;
-    p->class_count[c] = k;
-    for (int64_t j = 0; j < k; j += tpb)
-      tasks.push_back(Task{first + j, (int32_t)std::min<int64_t>(tpb, k - j), c});
-    p->args.alt[c] = shape & 1;
+    p->class_count[c] = (int64_t)item_off.size() - first;
   }
-  p->ntasks = (int)tasks.size();
 
   int cus = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -377,38 +427,29 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
     free_ragged(p);
     return hip_fail(e);
   }
-  p->grid = std::max(1, std::min(2 * cus, p->ntasks));  // two workgroups per CU
-
-  // List schedule (Graham's longest-processing-time rule): tasks, longest
-  // length first, each go to the workgroup with the least work so far.  A
-  // task costs its shape's measured duration, scaled down for a partly
-  // filled task: half of it (the loads and stores) is taken as proportional to
-  // the live transforms, the other half (the arithmetic of every slot) not.
-  // Each workgroup's tasks are then laid out contiguously, still longest
-  // length first.
-  std::vector<int> owner(tasks.size());
-  {
-    using Load = std::pair<double, int>;
-    std::priority_queue<Load, std::vector<Load>, std::greater<Load>> heap;
-    for (int w = 0; w < p->grid; ++w) heap.push(Load{0, w});
-    std::vector<double> cost(tasks.size());
-    std::vector<size_t> order(tasks.size());
-    for (size_t i = 0; i < tasks.size(); ++i) {
-      const Task& tk = tasks[i];
-      const int shape = p->shape_of_class[tk.cls];
-      const double fill = double(tk.count) / kShapes[shape].tpb;
-      cost[i] = kShapeTaskUs[shape] * (0.5 + 0.5 * fill);
-      order[i] = i;
-    }
-    std::stable_sort(order.begin(), order.end(),
-                     [&](size_t a, size_t b) { return cost[a] > cost[b]; });
-    for (size_t i : order) {
-      Load l = heap.top();
-      heap.pop();
-      owner[i] = l.second;
-      heap.push(Load{l.first + cost[i], l.second});
+  Layout layout = lay_out(p->class_count, p->shape_of_class, cus);
+  if (!named[5]) {
+    // The two shapes of 8192 points cost about the same per transform, but A
+    // takes two of them in a task: whichever grain the batch finishes earlier
+    // with.  us on an MI355X, rows from HBM, A / B: 850 lengths 18.7 / 18.6, 1000
+    // 21.6 / 19.9, 1200 24.5 / 22.2, 1500 27.0 / 31.0, 2000 36.7 / 40.9, 2400 47.9
+    // / 45.0.
+    int other[kClasses];
+    std::copy(std::begin(p->shape_of_class), std::end(p->shape_of_class), other);
+    other[5] ^= 1;
+    Layout alternative = lay_out(p->class_count, other, cus);
+    if (alternative.finish < layout.finish) {
+      layout = std::move(alternative);
+      p->shape_of_class[5] = other[5];
     }
   }
+  for (int c = 0; c < kClasses; ++c) p->args.alt[c] = p->shape_of_class[c] & 1;
+  std::vector<Task>& tasks = layout.tasks;
+  const std::vector<int>& owner = layout.owner;
+  p->ntasks = (int)tasks.size();
+  p->grid = layout.grid;
+  // Each workgroup's tasks are laid out contiguously, still longest length
+  // first.
   std::vector<int> wg_begin(p->grid + 1, 0);
   for (int w : owner) ++wg_begin[w + 1];
   for (int w = 0; w < p->grid; ++w) wg_begin[w + 1] += wg_begin[w];

@@ -4,6 +4,7 @@ import statistics
 import pytest
 
 import paper_2603_27569_amd as sf
+from paper_2603_27569_amd import workloads
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -48,3 +49,30 @@ def test_matrix_cores_keep_up_with_the_vector_units():
                       for io in (sf.FFT_IO_C16, sf.FFT_IO_C16_MMA))
     p.close()
     assert matrix <= 1.06 * vector, (matrix, vector)
+
+
+@pytest.mark.parametrize("count", [1200, 1500])
+def test_ragged_plan_takes_the_grain_that_fits(count):
+    """8192-point transforms go one or two to a task; which is better depends on
+    how the batch divides over the chip (1200 lengths 22.2 / 24.5 us, 1500 31.0 /
+    27.0).  A plan left to itself is as good as the better of the two; 4% is
+    well under what the other grain costs and above what two runs differ by."""
+    sizes = [int(s) for s in workloads.ragged_sizes(count, 1005)]
+    total, k = sum(sizes), 12
+    x = torch.randn(k, total, dtype=torch.complex64, device=DEV)
+    y = torch.empty_like(x)
+
+    def us(shape):
+        sf.fft_tune_clear_ragged()
+        if shape:
+            sf.fft_tune_set_ragged(8192, shape)
+        p = sf.RaggedPlan(sizes)
+        t = _us(lambda i, st: p.exec_direct(x[i % k].data_ptr(), y[i % k].data_ptr(), st), k)
+        p.close()
+        return t
+
+    try:
+        named = [us(shape) for shape in sf.fft_ragged_shapes(8192)]
+        assert us(None) <= 1.04 * min(named), named
+    finally:
+        sf.fft_tune_clear_ragged()
