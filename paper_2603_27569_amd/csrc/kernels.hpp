@@ -440,29 +440,38 @@ __device__ __forceinline__ void fused_loss_sum(float* scratch, float* total_out,
   // v + h for h = 512, 256, ..., 1).  Thread tid plays lanes tid + j THREADS.
   static_assert(1024 % S::THREADS == 0 && S::THREADS % 64 == 0, "lane mapping");
   static_assert(S::TPB * S::LDS_ELEMS * sizeof(c32) >= S::THREADS * sizeof(float), "tree");
-  // A lane's loads bypass the L2, about a microsecond each: 16 in flight per
-  // thread, added in their order.
   constexpr int V = 1024 / S::THREADS, U = 16 / V;
+  const auto row = [&](int64_t base, int j) {
+    const int64_t i = base + tid + j * S::THREADS;
+    return i < rows_all ? __hip_atomic_load(row_loss_all + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+  };
   float v[V];
+  if (rows_all <= 1024) {
+    // The one step's own few instructions: the last workgroup fetches them
+    // from memory while the launch waits for it (loss only, us on an MI355X,
+    // through the longer code below / here: 1024 x 64 5.33 / 5.09, 2048 x 100
+    // 6.14 / 5.82, 4096 x 24 6.64 / 6.36; with the gradient 2048 x 100 7.51 / 6.93).
 #pragma unroll
-  for (int j = 0; j < V; ++j) v[j] = 0.f;
-  for (int64_t base = 0; base < rows_all; base += 1024 * U) {
-    float q[U][V] = {};
+    for (int j = 0; j < V; ++j) v[j] = row(0, j);
+  } else {
+    // A lane's loads bypass the L2, about a microsecond each: 16 in flight per
+    // thread, added in their order.
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (base + 1024 * u >= rows_all) break;  // uniform
+    for (int j = 0; j < V; ++j) v[j] = 0.f;
+    for (int64_t base = 0; base < rows_all; base += 1024 * U) {
+      float q[U][V] = {};
 #pragma unroll
-      for (int j = 0; j < V; ++j) {
-        const int64_t i = base + 1024 * u + tid + j * S::THREADS;
-        if (i < rows_all)
-          q[u][j] = __hip_atomic_load(row_loss_all + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int u = 0; u < U; ++u) {
+        if (base + 1024 * u >= rows_all) break;  // uniform
+#pragma unroll
+        for (int j = 0; j < V; ++j) q[u][j] = row(base + 1024 * u, j);
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < V; ++j)
+          v[j] += q[u][j];  // (a missing row's zero changes nothing: v starts at +0)
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < V; ++j)
-        v[j] += q[u][j];  // (a missing row's zero changes nothing: v starts at +0)
   }
 #pragma unroll
   for (int h = V / 2; h > 0; h >>= 1)  // tree steps h * THREADS, inside a thread
