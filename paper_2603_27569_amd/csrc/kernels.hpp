@@ -235,7 +235,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham_io(const uint32
       for (int m = 0; m < S::E; ++m) a[m] = IO::load(src.ld32<row_policy<S>()>(voff, 4 * in_position<S>(0, m)));
     }
   }
-  run_passes<S, INV>(a, lds, tw, t);
+  run_passes<RoundedRoots<S>, INV>(a, lds, tw, t);
   if (live) {
     const Buf dst(out + row0 * S::N);
     const int voff = 4 * (slot * S::N + out_position<S>(t, 0));
@@ -326,6 +326,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham_stream(const vo
                                                                  const c32* tw, int64_t rows,
                                                                  int64_t stride) {
   using R = io_raw<IO>;
+  using P = std::conditional_t<sizeof(R) == 8, S, RoundedRoots<S>>;
   constexpr int B = (int)sizeof(R);
   constexpr int D = S::STREAM_DEPTH;  // rows in flight ahead of the one computed
   constexpr int NB = D + 1;           // register buffers, used round-robin
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham_stream(const vo
       c32 a[S::E];
 #pragma unroll
       for (int m = 0; m < S::E; ++m) a[m] = IO::load(buf[s][m]);
-      run_passes_preloaded<S, INV>(a, w, lds, tw, t);
+      run_passes_preloaded<P, INV>(a, w, lds, tw, t);
       const Buf o(dst + r * (S::N * B));
 #pragma unroll
       for (int m = 0; m < S::E; ++m) {

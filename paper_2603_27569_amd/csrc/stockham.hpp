@@ -85,8 +85,9 @@ constexpr double sin_pi16(int k) { return cos_pi16(k + 24); }
 // errors without and with it: radix 16.32.32 at 16384 points 1.33e-7 and
 // 1.25e-7, 16.16.16 at 4096 1.22e-7 and 1.16e-7, 32 x 32 columns at 2^20 1.68e-7
 // and 1.55e-7; the radix-8 plans of 16384 and 4096 have 1.31e-7 and 1.21e-7.
+// Without EXACT it is left out (RoundedRoots).
 // (a v as v + (a - 1) v would cost nothing, but makes a NaN of an infinite v.)
-template <int R, int K, bool INV>
+template <int R, int K, bool INV, bool EXACT>
 __device__ __forceinline__ c32 mul_root(c32 v) {
   static_assert(32 % R == 0 && K >= 0 && 4 * K <= 3 * R, "roots beyond W_32 are not tabulated");
   constexpr int k32 = K * 32 / R;
@@ -97,7 +98,7 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
     constexpr bool by_c = c * c >= s * s;
     constexpr double a = by_c ? c : s, b = by_c ? s : c;  // |a| >= |b|
     constexpr float ah = (float)a, al = (float)(a - (double)ah), bf = (float)b;
-    constexpr bool close = a * a > 0.75;  // +-cos(pi / 8), +-cos(pi / 16)
+    constexpr bool close = EXACT && a * a > 0.75;  // +-cos(pi / 8), +-cos(pi / 16)
     const auto part = [](float big, float small) {  // a big + b small
       float r = bf * small;
       if constexpr (close) r = __builtin_fmaf(al, big, r);
@@ -124,16 +125,16 @@ __device__ __forceinline__ c32 mul_root(c32 v) {
 // filter 8192 x 300 16.4 -> 16.7, binary16 4096 x 2048 13.6 -> 13.6, 2000 ragged
 // transforms 36.2 -> 37.1.
 
-template <int R, bool INV>
+template <int R, bool INV, bool EXACT = true>
 struct Dft;
 
-template <bool INV>
-struct Dft<1, INV> {
+template <bool INV, bool EXACT>
+struct Dft<1, INV, EXACT> {
   __device__ __forceinline__ static void run(c32 (&)[1]) {}
 };
 
-template <bool INV>
-struct Dft<2, INV> {
+template <bool INV, bool EXACT>
+struct Dft<2, INV, EXACT> {
   __device__ __forceinline__ static void run(c32 (&v)[2]) {
     c32 a = v[0], b = v[1];
     v[0] = cadd(a, b);
@@ -141,14 +142,14 @@ struct Dft<2, INV> {
   }
 };
 
-template <int R, bool INV>
+template <int R, bool INV, bool EXACT>
 struct Dft {
   static constexpr int H = R / 2, Q = R / 4;
   template <int K>
   __device__ __forceinline__ static void combine(c32 (&v)[R], const c32 (&u)[H], const c32 (&z)[Q],
                                                  const c32 (&y)[Q]) {
     if constexpr (K < Q) {
-      const c32 zr = mul_root<R, K, INV>(z[K]), yr = mul_root<R, 3 * K, INV>(y[K]);
+      const c32 zr = mul_root<R, K, INV, EXACT>(z[K]), yr = mul_root<R, 3 * K, INV, EXACT>(y[K]);
       const c32 p = cadd(zr, yr), m = mul_w4<INV>(csub(zr, yr));
       v[K] = cadd(u[K], p);
       v[K + H] = csub(u[K], p);
@@ -166,9 +167,9 @@ struct Dft {
       z[i] = v[4 * i + 1];
       y[i] = v[4 * i + 3];
     }
-    Dft<H, INV>::run(u);
-    Dft<Q, INV>::run(z);
-    Dft<Q, INV>::run(y);
+    Dft<H, INV, EXACT>::run(u);
+    Dft<Q, INV, EXACT>::run(z);
+    Dft<Q, INV, EXACT>::run(y);
     combine<0>(v, u, z, y);
   }
 };
@@ -314,6 +315,18 @@ template <class S, class = void>
 struct double_buffered : std::false_type {};
 template <class S>
 struct double_buffered<S, std::void_t<decltype(S::DB)>> : std::integral_constant<bool, S::DB> {};
+
+// Roots as FP32 rounds them, in the transforms of rows stored in 16 bits: the
+// result's own rounding is a thousand times larger, and the vector units bound
+// these kernels.
+template <class Base>
+struct RoundedRoots : Base {
+  static constexpr bool ROUNDED_ROOTS = true;
+};
+template <class S, class = void>
+struct rounded_roots : std::false_type {};
+template <class S>
+struct rounded_roots<S, std::void_t<decltype(S::ROUNDED_ROOTS)>> : std::true_type {};
 
 // Split exchange: every exchange sends the real parts of the whole transform
 // through the LDS, then the imaginary parts: half the space like two rounds
@@ -570,7 +583,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
           for (int r = 1; r < R; ++r) v[r] = ctw<INV>(v[r], wb[r - 1]);
         }
       }
-      Dft<R, INV>::run(v);
+      Dft<R, INV, !rounded_roots<S>::value>::run(v);
 #pragma unroll
       for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
     }
@@ -589,7 +602,7 @@ __device__ __forceinline__ void pass_compute(c32 (&a)[S::E], c32 (&w)[S::TW_REGS
     c32 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = a[b + r * BPT];
-    Dft<R, INV>::run(v);
+    Dft<R, INV, !rounded_roots<S>::value>::run(v);
 #pragma unroll
     for (int r = 0; r < R; ++r) a[b + r * BPT] = v[r];
   }
