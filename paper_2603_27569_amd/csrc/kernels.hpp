@@ -540,7 +540,12 @@ struct CountProbe {
 // index mod kTotalGroups, each on its own 256-byte line), and each group's
 // last one on a second-level counter, so no single address takes every
 // workgroup's atomic.  counters: kTotalGroups * 64 + 1 zeroed words, left zeroed.
-template <class S>
+// GRAD false is the loss alone, a kernel of its own: in the one with the adjoint
+// it ran with that one's registers (us on an MI355X, there / here: 8192 x 1000
+// 24.5 / 22.8, 16384 x 1000 47.9 / 46.4).  There the test of grad, always true,
+// stays: it keeps the compiler from moving loads and registers of one transform
+// into the other (4096 x 2048 31.6 us with it, 34.6 without).
+template <class S, bool GRAD>
 __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
     const c32* x, const float* __restrict__ w, const float* __restrict__ scale, c32* grad,
     float* row_loss, const c32* tw, int64_t rows, float* total_out, unsigned* counters,
@@ -592,7 +597,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
       for (int i = 0; i < S::T / 64; ++i) total += red[w0 + i];
     }
     if (total_out != nullptr)
-      published = fused_loss_publish<early>(&row_loss[row], total);
+      published = fused_loss_publish<early && GRAD>(&row_loss[row], total);
     else
       row_loss[row] = total;
   }
@@ -601,21 +606,21 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy(
   // during the adjoint or behind it.
   const bool counts = total_out != nullptr && tid == 0;
   CountProbe<2 * S::P - 2> probe{counters, gbase + blockIdx.x, counts, published};
-  if (grad != nullptr) {  // uniform across the launch
+  if (GRAD && grad != nullptr) {  // uniform across the launch
     if constexpr (early)
       run_passes<S, true>(a, lds, tw, t, &probe);
     else
       run_passes<S, true>(a, lds, tw, t);
   }
-  if ((!early || grad == nullptr) && total_out != nullptr) {  // uniform across the launch
-    fused_loss_published<early>(published);
+  if ((!early || !GRAD || grad == nullptr) && total_out != nullptr) {  // uniform across the launch
+    fused_loss_published<early && GRAD>(published);
     if constexpr (S::TPB > 1) __syncthreads();  // ... every slot's
     if (tid == 0) probe.arrived = fused_loss_arrive(counters, gbase + blockIdx.x);
   }
   // With the answer in, the group's last goes on to the second level before
   // its stores, behind which that round trip would wait.
   if (early && counts) is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
-  if (grad != nullptr) buffer_store_row<S>(a, Buf(grad + row0 * S::N), slot * S::N, t, live);
+  if (GRAD && grad != nullptr) buffer_store_row<S>(a, Buf(grad + row0 * S::N), slot * S::N, t, live);
   if (total_out != nullptr) {
     if (!early && tid == 0)
       is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
@@ -633,7 +638,8 @@ hipError_t launch_spectral_energy(const void* x, const float* w, const float* sc
   for (int64_t g0 = 0; g0 < groups; g0 += cap) {
     const int64_t g = groups - g0 < cap ? groups - g0 : cap;
     const int64_t r0 = g0 * S::TPB;
-    k_spectral_energy<S><<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
+    const auto kernel = grad ? &k_spectral_energy<S, true> : &k_spectral_energy<S, false>;
+    kernel<<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
         static_cast<const c32*>(x) + r0 * S::N, w, scale,
         grad ? static_cast<c32*>(grad) + r0 * S::N : nullptr, row_loss + r0,
         static_cast<const c32*>(tw), batch - r0, total, counters, row_loss, batch,
@@ -649,7 +655,7 @@ hipError_t launch_spectral_energy(const void* x, const float* w, const float* sc
 // where a workgroup per row runs every row's loads, arithmetic and stores in
 // lockstep.  The twiddles and the squared weights of the lane's positions
 // are loaded once per workgroup.  Same outputs as k_spectral_energy.
-template <class S>
+template <class S, bool GRAD>
 __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_stream(
     const c32* x, const float* __restrict__ w, const float* __restrict__ scale, c32* grad,
     float* row_loss, const c32* tw, int64_t rows, int64_t stride, float* total_out,
@@ -727,7 +733,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_stream(
         else
           row_loss[r] = total;
       }
-      if (grad != nullptr) {  // uniform across the launch
+      if (GRAD && grad != nullptr) {  // uniform across the launch
         run_passes_preloaded<S, true>(a, tws, lds, tw, t);
         const Buf o(grad + r * S::N);
 #pragma unroll
@@ -751,7 +757,8 @@ hipError_t launch_spectral_energy_stream(const void* x, const float* w, const fl
                                          const void* tw, int64_t batch, hipStream_t s) {
   int64_t g = (int64_t)device_cus() * streamed<S>::value;
   if (g > batch) g = batch;
-  k_spectral_energy_stream<S><<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
+  const auto kernel = grad ? &k_spectral_energy_stream<S, true> : &k_spectral_energy_stream<S, false>;
+  kernel<<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
       static_cast<const c32*>(x), w, scale, static_cast<c32*>(grad), row_loss,
       static_cast<const c32*>(tw), batch, g, total, counters);
   return hipGetLastError();

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_stockham_wx(const void* 
 // leg r at h + 64 m + 512 r) is the input register map of the adjoint, so
 // the adjoint runs on the registers in place; the weight of each value is
 // read at its output position.
-template <class S>
+template <class S, bool GRAD>
 __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_wx(
     const c32* x, const float* __restrict__ w, const float* __restrict__ scale, c32* grad,
     float* row_loss, const c32* tw, float* total_out, unsigned* counters, float* row_loss_all,
@@ -415,19 +415,21 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_spectral_energy_wx(
 #pragma unroll
     for (int i = 0; i < S::THREADS / 64; ++i) total += red[i];
     if (total_out != nullptr)
-      published = fused_loss_publish<true>(&row_loss[row], total);
+      published = fused_loss_publish<GRAD>(&row_loss[row], total);
     else
       row_loss[row] = total;
   }
   // Counted during the adjoint, as in k_spectral_energy.
   const bool counts = total_out != nullptr && tid == 0;
   CountProbe<4> probe{counters, gbase + blockIdx.x, counts, published};
-  if (grad != nullptr)  // uniform across the launch
+  if (GRAD && grad != nullptr) {  // uniform across the launch
     wx_passes<S, true>(R, L, lds, &probe);
-  else
-    probe.mark(4);
+  } else if (counts) {
+    fused_loss_published<GRAD>(published);
+    probe.arrived = fused_loss_arrive(counters, gbase + blockIdx.x);
+  }
   if (counts) is_last = fused_loss_last(probe.arrived, counters, groups_all, gbase + blockIdx.x);
-  if (grad != nullptr) wx_store<S, IoF32>(R, L, grad, row);
+  if (GRAD && grad != nullptr) wx_store<S, IoF32>(R, L, grad, row);
   if (total_out != nullptr) {  // uniform across the launch
     __syncthreads();  // is_last visible; the LDS free for the sum's tree
     if (is_last) fused_loss_sum<S>(reinterpret_cast<float*>(lds), total_out, row_loss_all, rows_all);
@@ -441,7 +443,8 @@ hipError_t launch_spectral_energy_wx(const void* x, const float* w, const float*
   const int64_t cap = max_groups_per_launch();
   for (int64_t r0 = 0; r0 < batch; r0 += cap) {
     const int64_t g = batch - r0 < cap ? batch - r0 : cap;
-    k_spectral_energy_wx<S><<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
+    const auto kernel = grad ? &k_spectral_energy_wx<S, true> : &k_spectral_energy_wx<S, false>;
+    kernel<<<dim3((unsigned)g), dim3(S::THREADS), 0, s>>>(
         static_cast<const c32*>(x) + r0 * 4096, w, scale,
         grad ? static_cast<c32*>(grad) + r0 * 4096 : nullptr, row_loss + r0,
         static_cast<const c32*>(tw), total, counters, row_loss, batch, (unsigned)batch,
