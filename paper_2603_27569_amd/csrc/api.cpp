@@ -204,24 +204,28 @@ struct BuiltinEntry {
   const char* name;
 };
 const BuiltinEntry kBuiltin[] = {
-    {256, 1, 160, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 161, 256, "n256_e16_b4_p4_r16.16_pt_ol"},
+    {256, 1, 256, "n256_e4_b4_p4_r4.4.4.4_pt"},
     {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4"},
     {256, 385, 512, "n256_e4_b4_p4_r4.4.4.4_pt"},
     {256, 513, 1024, "n256_e4_b4_p4_r4.4.4.4"},
-    {256, 1025, 2048, "n256_e16_b4_p4_r16.16"},
-    {256, 2049, 6144, "n256_e16_b4_p4_r16.16_pt"},
+    {256, 1025, 3072, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 3073, 4096, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {256, 4097, 6144, "n256_e16_b4_p4_r16.16_pt"},
     {256, 6145, 8192, "n256_e16_b4_p4_r16.16_pt_ol"},
     {256, 8193, INT64_MAX, "n256_e8_b8_p4_r8.8.4_pt_ol"},
-    {512, 1, 512, "n512_e4_b2_p4_r4.4.4.4.2"},
-    {512, 513, 1024, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {512, 1025, 1536, "n512_e16_b2_p4_r16.16.2"},
-    {512, 1537, 2048, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 1, 16, "n512_e8_b4_p4_r8.8.8"},
+    {512, 17, 32, "n512_e4_b2_p4_r4.4.4.4.2"},
+    {512, 33, 160, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 161, 256, "n512_e8_b4_p4_r8.8.8"},
+    {512, 257, 384, "n512_e4_b2_p4_r4.4.4.4.2"},
+    {512, 385, 512, "n512_e8_b4_p4_r8.8.8"},
+    {512, 513, 2048, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {512, 2049, 4096, "n512_e16_b2_p4_r16.16.2_pt"},
     {512, 4097, 8192, "n512_e32_b4_p4_r32.16_pt"},
     {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {1024, 1, 16, "n1024_e4_b1_p4_r4.4.4.4.4"},
-    {1024, 17, 64, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 17, 32, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 33, 64, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
     {1024, 65, 256, "n1024_e4_b1_p4_r4.4.4.4.4"},
     {1024, 257, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
     {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
@@ -250,16 +254,16 @@ const BuiltinEntry kBuiltin[] = {
     {4096, 3073, 4096, "n4096_e16_b1_px_r16.16.16_db_pt_tall_st2d1"},
     {4096, 4097, 8192, "n4096_e16_b1_p5_r16.16.16_pt"},
     {4096, 8193, INT64_MAX, "n4096_e8_b1_p4_r8.8.8.8_pt_tall_st1d1"},
-    {8192, 1, 16, "fs8192_4x2048"},
-    {8192, 17, 160, "n8192_e16_b1_p4_r16.16.16.2_pt"},
+    {8192, 1, 32, "fs8192_4x2048"},
+    {8192, 33, 160, "n8192_e16_b1_p4_r16.16.16.2_pt"},
     {8192, 161, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
     {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
     {8192, 513, 768, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
     {8192, 769, 1024, "n8192_e32_c4_b1_p4_r8.8.8.16"},
     {8192, 1025, 1536, "n8192_e32_c2_b1_p4_r16.16.32_pt_ol"},
     {8192, 1537, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
-    {16384, 1, 16, "fs16384_8x2048"},
-    {16384, 17, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
+    {16384, 1, 32, "fs16384_8x2048"},
+    {16384, 33, 160, "n16384_e32_b1_p4_r32.32.16_pt"},
     {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
     {16384, 257, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
     {16384, 513, 768, "n16384_e64_c2_b1_p4_r32.32.16_pt_ol"},
@@ -284,16 +288,14 @@ const BuiltinEntry kBuiltinFilter[] = {
     {256, 161, 256, "n256_e4_b4_p4_r4.4.4.4"},
     {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4_pt"},
     {256, 385, 1024, "n256_e4_b4_p4_r4.4.4.4"},
-    {256, 1025, 2048, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 2049, 3072, "n256_e16_b4_p4_r16.16_pt"},
-    {256, 3073, 4096, "n256_e16_b4_p4_r16.16"},
+    {256, 1025, 3072, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 3073, 4096, "n256_e8_b8_p4_r8.8.4_pt_ol"},
     {256, 4097, 8192, "n256_e16_b4_p4_r16.16_pt"},
     {256, 8193, INT64_MAX, "n256_e16_b4_p4_r16.16_pt_ol"},
-    {512, 1, 512, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 513, 1024, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {512, 1025, 1536, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 1537, 2048, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {512, 2049, 4096, "n512_e16_b2_p4_r16.16.2_pt"},
+    {512, 1, 256, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 257, 512, "n512_e8_b4_p4_r8.8.8"},
+    {512, 513, 3072, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 3073, 4096, "n512_e16_b2_p4_r16.16.2_pt"},
     {512, 4097, 8192, "n512_e32_b4_p4_r32.16_pt"},
     {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {1024, 1, 768, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
@@ -316,8 +318,8 @@ const BuiltinEntry kBuiltinFilter[] = {
     {4096, 1025, 3072, "n4096_e32_c2_b1_p4_r16.16.16_pt_ol"},
     {4096, 3073, 4096, "n4096_e32_c2_b1_p4_r16.16.16_pt"},
     {4096, 4097, INT64_MAX, "n4096_e32_b1_p4_r16.16.16_pt_pl"},
-    {8192, 1, 64, "n8192_e16_b1_p4_r16.16.16.2_pt"},
-    {8192, 65, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
+    {8192, 1, 16, "n8192_e16_b1_p4_r16.16.16.2_pt"},
+    {8192, 17, 256, "n8192_e8_b1_p4_r8.8.8.8.2_pt"},
     {8192, 257, 512, "n8192_e32_b1_p4_r32.16.16_pt"},
     {8192, 513, 1536, "n8192_e32_c2_b1_p4_r16.16.32_pt_ol"},
     {8192, 1537, INT64_MAX, "n8192_e32_c2_b1_p4_r16.16.32_pt"},
@@ -325,9 +327,7 @@ const BuiltinEntry kBuiltinFilter[] = {
     {16384, 161, 256, "n16384_e16_b1_p4_r16.16.16.4_pt"},
     {16384, 257, 512, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
     {16384, 513, 768, "n16384_e32_c2_b1_p4_r16.16.16.4_pt"},
-    {16384, 769, 1024, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
-    {16384, 1025, 2048, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
-    {16384, 2049, 4096, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
+    {16384, 769, 4096, "n16384_e64_c2_b1_p4_r32.32.16_pt"},
     {16384, 4097, INT64_MAX, "n16384_e64_c2_b1_p4_r16.32.32_pt"},
 };
 
@@ -336,18 +336,17 @@ const BuiltinEntry kBuiltinFilter[] = {
 // move, so the balance between memory and arithmetic, and with it the best
 // shape, differs from the FP32 transform's.
 const BuiltinEntry kBuiltinStorage16[] = {
-    {256, 1, 256, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 1, 16, "n256_e4_b4_p4_r4.4.4.4_pt"},
+    {256, 17, 64, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 65, 256, "n256_e4_b4_p4_r4.4.4.4_pt"},
     {256, 257, 384, "n256_e4_b4_p4_r4.4.4.4"},
     {256, 385, 2048, "n256_e4_b4_p4_r4.4.4.4_pt"},
-    {256, 2049, 4096, "n256_e16_b4_p4_r16.16"},
-    {256, 4097, 8192, "n256_e8_b8_p4_r8.8.4_pt_ol"},
+    {256, 2049, 3072, "n256_e4_b4_p4_r4.4.4.4"},
+    {256, 3073, 8192, "n256_e8_b8_p4_r8.8.4_pt_ol"},
     {256, 8193, INT64_MAX, "n256_e16_b4_p4_r16.16_pt_ol"},
-    {512, 1, 384, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {512, 385, 512, "n512_e4_b2_p4_r4.4.4.4.2_pt"},
-    {512, 513, 4096, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 1, 4096, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {512, 4097, 6144, "n512_e16_b2_p4_r16.16.2_pt"},
-    {512, 6145, 8192, "n512_e16_b2_p4_r16.16.2_pt_ol"},
-    {512, 8193, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
+    {512, 6145, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {1024, 1, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
     {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
     {1024, 769, 1024, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
@@ -362,8 +361,10 @@ const BuiltinEntry kBuiltinStorage16[] = {
     {2048, 6145, 8192, "n2048_e32_c2_b1_p4_r16.16.8_pt_ol"},
     {2048, 8193, INT64_MAX, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
     {4096, 1, 16, "n4096_e8_b1_p4_r8.8.8.8_pt"},
-    {4096, 17, 64, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
-    {4096, 65, 256, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {4096, 17, 32, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
+    {4096, 33, 64, "n4096_e8_b1_p4_r8.8.8.8_pt"},
+    {4096, 65, 160, "n4096_e8_b1_p4_r8.8.8.8_pt_tall"},
+    {4096, 161, 256, "n4096_e8_b1_p4_r8.8.8.8_pt"},
     {4096, 257, 512, "n4096_e16_b1_px_r16.16.16_db_pt"},
     {4096, 513, 768, "n4096_e16_b1_p5_r16.16.16_pt"},
     {4096, 769, 1024, "n4096_e32_b1_p4_r16.16.16_pt"},
@@ -394,10 +395,13 @@ const BuiltinEntry kBuiltinFused[] = {
     {512, 17, 3072, "n512_e8_b4_p4_r8.8.8_pt_ol"},
     {512, 3073, 4096, "n512_e8_b4_p4_r8.8.8_pt"},
     {512, 4097, INT64_MAX, "n512_e8_b4_p4_r8.8.8_pt_ol"},
-    {1024, 1, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 1, 16, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
+    {1024, 17, 64, "n1024_e4_b1_p4_r4.4.4.4.4"},
+    {1024, 65, 512, "n1024_e4_b1_p4_r4.4.4.4.4_pt"},
     {1024, 513, 768, "n1024_e16_b1_p4_r16.16.4_pt_ol"},
-    {1024, 769, 1536, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
-    {1024, 1537, 2048, "n1024_e16_b1_p4_r16.16.4_pt"},
+    {1024, 769, 1024, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
+    {1024, 1025, 1536, "n1024_e8_b2_p4_r8.8.8.2_pt_ol"},
+    {1024, 1537, 2048, "n1024_e16_b4_p4_r16.16.4_pt"},
     {1024, 2049, 3072, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
     {1024, 3073, 4096, "n1024_e32_b4_p4_r32.32_pt"},
     {1024, 4097, INT64_MAX, "n1024_e16_b4_p4_r16.16.4_pt_ol"},
@@ -406,7 +410,7 @@ const BuiltinEntry kBuiltinFused[] = {
     {2048, 1537, 6144, "n2048_e16_b1_p4_r16.16.8_pt_ol"},
     {2048, 6145, INT64_MAX, "n2048_e16_b1_p4_r16.16.8_pt"},
     {4096, 1, 256, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
-    {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt_tall"},
+    {4096, 257, 384, "n4096_e16_b1_px_r16.16.16_db_pt"},
     {4096, 385, 512, "n4096_e8_b1_px_r8.8.8.8_pt_wx1"},
     {4096, 513, 768, "n4096_e16_b1_p5_r16.16.16_pt"},
     {4096, 769, 1024, "n4096_e16_b1_px_r16.16.16_pt"},

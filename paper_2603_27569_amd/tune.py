@@ -25,13 +25,14 @@ scratch and LDS of its compiled kernel as the runtime reports them
 Timing: back-to-back launches captured into a HIP graph (so the host's launch
 rate is no limit), bracketed by HIP events; the median of three repeats, each
 at least REPEAT_US of GPU time; candidates within 3% of the best are timed
-again with three times the launches before one is chosen.  Each candidate is
-timed at two batches of the bucket and there twice, over a ring of independent
-buffers larger than the Infinity
-Cache (rows come from HBM) and over three inputs and two outputs (rows just
-produced, as far as they fit the cache), and scored by the geometric mean
-("us").  Every variant computes the same transform (the parity tests check
-each one against the FP64 reference), so the search is on speed alone.
+again with three times the launches.  Each candidate is timed at two batches
+of the bucket and there twice, over a ring of independent buffers (1 GiB of
+them, so rows come from HBM, or RING_MAX pairs: launches below 640 KiB find
+their rows cached all the same) and over three inputs and two outputs (rows
+just produced, as far as they fit the cache), and scored by the geometric mean
+("us"); the fused kernel with its gradient and without.  Every variant computes
+the same transform (the parity tests check each one against the FP64 reference),
+so the search is on speed alone.
 
 Usage: python -m paper_2603_27569_amd.tune [--out tune_gfx950.json] [--quick]
        python -m paper_2603_27569_amd.tune --run-variants N BATCH [--iters K]
@@ -61,7 +62,7 @@ SIZES_LARGE = tuple(1 << e for e in range(15, 21))
 # power of two a bucket ends at and a batch that is no multiple of the CU
 # count, so that no choice rests on a last round of workgroups that happens to
 # be full.
-BUCKETS = ((1, 16, (3, 8)), (17, 64, (24, 64)), (65, 160, (90, 128)), (161, 256, (200, 256)),
+BUCKETS = ((1, 16, (3, 8)), (17, 32, (24, 32)), (33, 64, (48, 64)), (65, 160, (90, 128)), (161, 256, (200, 256)),
            (257, 384, (290, 370)), (385, 512, (430, 512)), (513, 768, (560, 720)), (769, 1024, (850, 1024)),
            (1025, 1536, (1100, 1450)), (1537, 2048, (1700, 2048)), (2049, 3072, (2300, 2900)),
            (3073, 4096, (3500, 4096)), (4097, 6144, (4700, 5900)), (6145, 8192, (7000, 8192)),
@@ -88,10 +89,10 @@ def _ring(torch, dev, n, batch):
     return xs, ys
 
 
-def _time(torch, stream, fn, iters, warmup=5, repeats=3):
+def _time(torch, stream, fn, iters, factor=1, warmup=5, repeats=3):
     """Median over `repeats` of the per-launch time of back-to-back launches
     (microseconds): a graph of at least `iters` launches, replayed so that a
-    repeat covers REPEAT_US of GPU time."""
+    repeat covers `factor` times REPEAT_US of GPU time."""
     per = max(15, iters)
     with torch.cuda.stream(stream):
         for i in range(warmup):
@@ -115,18 +116,18 @@ def _time(torch, stream, fn, iters, warmup=5, repeats=3):
 
     run(1)
     probe = max(run(1), 0.5)
-    times = max(1, min(2000, int(REPEAT_US / probe)) // per)
+    times = factor * max(1, math.ceil(min(2000, REPEAT_US / probe) / per))
     return statistics.median(run(times) for _ in range(repeats))
 
 
-def _time_both(torch, stream, call, xs, ys, iters):
+def _time_both(torch, stream, call, xs, ys, iters, factor=1):
     """Geometric mean of the per-launch times with rows from HBM (the whole
     ring) and with rows just produced (three inputs, two outputs).
     call(x, y) launches once."""
     k = len(xs)
-    cold = _time(torch, stream, lambda i: call(xs[i % k], ys[i % k]), k)
+    cold = _time(torch, stream, lambda i: call(xs[i % k], ys[i % k]), k, factor)
     m, o = min(3, k), min(2, k)
-    warm = _time(torch, stream, lambda i: call(xs[i % m], ys[i % o]), iters // 2)
+    warm = _time(torch, stream, lambda i: call(xs[i % m], ys[i % o]), iters // 2, factor)
     return math.sqrt(cold * warm)
 
 
@@ -147,7 +148,7 @@ def _tune_table(torch, stream, sizes, buckets, iters, log, label, value_bytes, r
     timed at the bucket's representative batches and scored by the geometric
     mean of its times; those within CLOSE of a batch's best are timed again
     there.  ring(n, batch) gives the buffers, plan(n, batch, name) a plan,
-    launch(n, batch) a function (plan, x, y) that launches once."""
+    launch(n, batch) the functions (plan, x, y) to time, which launch once."""
     entries = []
     for n in sizes:
         for bmin, bmax, representative in buckets:
@@ -155,13 +156,13 @@ def _tune_table(torch, stream, sizes, buckets, iters, log, label, value_bytes, r
             logs = {}
             for b in batches:
                 xs, ys = ring(n, b)
-                run = launch(n, b)
+                runs = launch(n, b)
 
                 def timed(name, factor=1):
                     p = plan(n, b, name)
-                    t = _time_both(torch, stream, lambda x, y: run(p, x, y), xs, ys, iters * factor)
+                    t = [_time_both(torch, stream, lambda x, y: run(p, x, y), xs, ys, iters, factor) for run in runs]
                     p.close()
-                    return t
+                    return math.prod(t) ** (1 / len(t))
 
                 times = {name: timed(name) for name in names(n)}
                 limit = min(times.values()) * CLOSE
@@ -216,7 +217,7 @@ def tune_plain(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=p
 
     entries = _tune_table(torch, stream, sizes, buckets, iters, log, "plain", 8,
                           lambda n, b: _ring(torch, dev, n, b), lambda n: list(dict(candidates(n))), plan,
-                          lambda n, b: lambda p, x, y: p.exec(x.data_ptr(), y.data_ptr(), cs))
+                          lambda n, b: (lambda p, x, y: p.exec(x.data_ptr(), y.data_ptr(), cs),))
     for e in entries:
         e["resources"] = {k: resources[k] for k in e["candidates"] if resources.get(k)}
     return entries
@@ -233,23 +234,29 @@ def tune_filter(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=
 
     def launch(n, b):
         h = torch.randn(n, dtype=torch.complex64, device=dev)
-        return lambda p, x, y: fft_exec_matched_filter(p.handle, x.data_ptr(), h.data_ptr(), y.data_ptr(), cs)
+        return (lambda p, x, y: fft_exec_matched_filter(p.handle, x.data_ptr(), h.data_ptr(), y.data_ptr(), cs),)
 
     return _tune_table(torch, stream, sizes, buckets, iters, log, "filter", 8,
                        lambda n, b: _ring(torch, dev, n, b), filter_candidates, _single_plan, launch)
 
 
 def tune_fused(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, log=print):
-    """The fused forward -> weight -> adjoint kernel (gradient and loss total
-    included) per length and batch bucket, over the single-pass variants."""
+    """The fused forward -> weight -> adjoint kernel per length and batch bucket,
+    over the single-pass variants: a training step runs it for the loss total
+    alone and then with the gradient, so a shape is scored by both calls."""
     cs = stream.cuda_stream
 
     def launch(n, b):
         w = torch.rand(n, dtype=torch.float32, device=dev)
         total = torch.empty(1, dtype=torch.float32, device=dev)
         rows = torch.empty(b, dtype=torch.float32, device=dev)
-        return lambda p, x, y: fft_exec_spectral_energy(p.handle, x.data_ptr(), w.data_ptr(), 0, y.data_ptr(),
-                                                        rows.data_ptr(), total.data_ptr(), cs)
+
+        def call(gradient):
+            return lambda p, x, y: fft_exec_spectral_energy(p.handle, x.data_ptr(), w.data_ptr(), 0,
+                                                            y.data_ptr() if gradient else 0, rows.data_ptr(),
+                                                            total.data_ptr(), cs)
+
+        return call(True), call(False)
 
     return _tune_table(torch, stream, sizes, buckets, iters, log, "fused", 8,
                        lambda n, b: _ring(torch, dev, n, b), fused_candidates, _single_plan, launch)
@@ -269,8 +276,8 @@ def tune_storage16(torch, dev, stream, sizes=SIZES, buckets=BUCKETS, iters=30, l
 
     return _tune_table(torch, stream, sizes, buckets, iters, log, "storage16", 4, ring,
                        lambda n: [nm for nm, algo in candidates(n) if algo == FFT_ALGO_SINGLE_PASS], _single_plan,
-                       lambda n, b: lambda p, x, y: fft_exec_io(p.handle, x.data_ptr(), y.data_ptr(),
-                                                                FFT_IO_C16, cs))
+                       lambda n, b: (lambda p, x, y: fft_exec_io(p.handle, x.data_ptr(), y.data_ptr(),
+                                                                 FFT_IO_C16, cs),))
 
 
 def tune_ragged(torch, dev, stream, sizes=None, iters=20, sweeps=2, log=print):
