@@ -359,7 +359,10 @@ int fft_set_launch_limit(int64_t max_groups);
  *   NUL-terminated); returns FFT_INVALID_ARGUMENT for a bad index or a
  *   buffer that is too small.  A single-pass variant states its shape
  *   (values_per_lane, lanes_per_transform, transforms_per_workgroup,
- *   radices, lds_layout, exchange_rounds, barriers, twiddle_schedule, ...),
+ *   radices, lds_layout, exchange_rounds, barriers, twiddle_schedule, ...;
+ *   "barriers" counts the points that order the LDS accesses of a
+ *   transform's exchanges: workgroup barriers, except that transforms of up
+ *   to 64 lanes run without any, in the order of their wave's accesses),
  *   whether it has the fused forward -> weight -> adjoint kernel
  *   ("fused_kernel") and also the matched filter ("fused_kernels"), its
  *   persistent workgroups per CU ("streamed", 0 for a workgroup per row),

@@ -1151,10 +1151,13 @@ extern "C" int fft_tune_clear(void) {
 // --------------------------------------------------------- introspection
 
 static int barriers_of(const SingleVariant& v) {
-  // Per exchange round one barrier after the writes and one after the reads,
-  // except after the reads of the last round of the last exchange (the last
-  // pass writes global memory directly, as the first pass reads it); with
-  // two alternating buffers only the one after the writes.
+  // The points that order the LDS accesses of a transform's exchanges:
+  // workgroup barriers, or for transforms of one wave's lanes (t <= 64) the
+  // order in which the LDS takes that wave's accesses (transform_sync).
+  // Per exchange round one after the writes and one after the reads, except
+  // after the reads of the last round of the last exchange (the last pass
+  // writes global memory directly, as the first pass reads it); with two
+  // alternating buffers only the one after the writes.
   if (v.npass < 2) return 0;
   // In-wave exchanges: only the middle exchange goes through the LDS, and
   // its buffer is not reused.

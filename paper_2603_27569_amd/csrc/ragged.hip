@@ -90,6 +90,9 @@ constexpr ShapeInfo info(const char* name) {
   return s;
 }
 
+// Tune files hold these names, so they outlive the shapes they were first given
+// to: c2 is an exchange through half a tile, in two rounds or, for the radix-32
+// plans of 8192 and 16384 points, in two parts.
 const ShapeInfo kShapes[kNumShapes] = {
     info<A256>("ragged_n256_e8"),          info<B256>("ragged_n256_e16"),
     info<A512>("ragged_n512_e32c2"),       info<B512>("ragged_n512_e16"),
