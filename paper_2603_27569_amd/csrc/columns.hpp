@@ -13,15 +13,15 @@
 // What bounds it: each stage reads and writes every byte once, so the floor is
 // two copies; a copy in the same access pattern takes 16.3 us per stage at
 // 2^16 x 101 rows and 39-43 us at 2^16 x 256 on an MI355X, the stages take
-// 17.4 + 18.3 and 44.8 + 41.3 us.  The arithmetic (VALU issue) of a stage is
-// about 40% of that and overlaps with it as far as the resident workgroups
-// (16 waves per CU, limited by 128 VGPRs and 34 or 68 KiB of LDS) are in
-// different phases; at 2^20 x 16 the grid is two rounds of them, and the
-// stages take 51 + 49 us.  Against three radix-4 or radix-8 passes per stage
+// 17.4 + 18.3 and 44.8 + 41.3 us.  The arithmetic (VALU issue) of a stage is 30
+// to 39% of its busy cycles (counted at 2^16 x 101 and 2^20 x 16) and overlaps
+// with the rest as far as the resident workgroups (16 waves per CU, limited by
+// 128 VGPRs and 34 or 68 KiB of LDS) are in different phases; at 2^20 x 16 the
+// grid is two rounds of them, and the stages take 51 + 50 us.  Against three radix-4 or radix-8 passes per stage
 // and a closing transpose through LDS (the shape before) the two-pass columns
 // measure 36.1 against 45.7 us (2^16 x 101), 37.4 against 45.5 (2^15 x 200),
-// 76 against 91 (2^17 x 101), 81 against 94 (2^18 x 51), 104 against 118
-// (2^20 x 16; 101.0 with split-radix DFTs), 28.8 against 37.9 (2^20 x 3) and
+// 76 against 91 (2^17 x 101), 81 against 94 (2^18 x 51), 101.3 against 118
+// (2^20 x 16), 28.8 against 37.9 (2^20 x 3) and
 // 8.4 against 11.9 (2^16 x 1).
 #pragma once
 
@@ -40,9 +40,12 @@ namespace stockfft {
 //
 // LDS layout: slot k KROW + t TILE + c for column c, one TILE-wide pad per k
 // row, so that the accesses with lanes c fastest hit every bank once in both
-// passes.  FLIP (stage 1) changes the lane order to t fastest for pass 1;
-// there the column is rotated by spread(k) inside its 16, which makes those
-// reads conflict-free too.
+// passes (no conflict counted in stage 2).  FLIP (stage 1) changes the lane
+// order to t fastest for pass 1; there the column is rotated by spread(k)
+// inside its 16, which gives the 32 lanes of a half wave 32 different slots
+// modulo the banks.  The counters still show those reads taking twice their
+// cycles, a third of stage 1's LDS cycles (64 of 192 per wave, split 128 of
+// 384); the LDS is busy for an eighth of that stage's cycles.
 template <int R0_, int R1_, int TILE_, bool SPLIT_, int WPE_>
 struct Col {
   static constexpr int R0 = R0_, R1 = R1_, TILE = TILE_, WPE = WPE_;

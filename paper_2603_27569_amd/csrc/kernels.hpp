@@ -15,7 +15,8 @@ namespace stockfft {
 // element is read once and every output element written once, so the hint
 // keeps them from displacing the shared twiddle tables and lets the output
 // drain to memory while the kernel still runs instead of at its end.  Loads
-// of rows that may still be in the Infinity Cache go without (stream_rows).  The
+// of rows that may still be in the Infinity Cache go without where that measured
+// faster (the ragged and matrix-core launches by stream_rows, the shapes _ol).  The
 // four-step's stride-N1 column loads keep ordinary accesses (their cache
 // lines are shared between workgroups; the hint there cost up to 1.5x at
 // N = 2^20), and so does its workspace, which the second stage reads back;
@@ -848,8 +849,8 @@ __global__ __launch_bounds__(S::THREADS, S::WPE) void k_four_step_columns(const 
   global_store_row<S, false>(a, y + (row * N1 + n1) * S::N, t, true);
 }
 
-// Length-N1 DFT in registers for the four-step second stage.  N1 <= 16: the
-// exact radix-2 DIT of Dft.  N1 = 32, 64: N1 = P Q with P = 16, i.e. P-point
+// Length-N1 DFT in registers for the four-step second stage.  N1 <= 16:
+// Dft itself.  N1 = 32, 64: N1 = P Q with P = 16, i.e. P-point
 // DFTs of the Q interleaved sub-sequences v[Q p + q], twiddles W_N1^{q kp}
 // (from wn, wn[j] = W_N1^j in the forward direction), then Q-point DFTs; the
 // result X[k] is left in v[slot(k)].

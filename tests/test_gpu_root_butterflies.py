@@ -1,7 +1,7 @@
 """Impulses through every root of the in-register DFTs: a 1 at element p gives
-e^{-+2 pi i p k / n} at every bin k, one product chain per bin.  The ragged and
-16-bit kernels run the fused root butterflies, the plain complex64 and the
-column kernels the product-first ones."""
+e^{-+2 pi i p k / n} at every bin k, one product chain per bin.  The ragged, the
+plain complex64 and the column kernels correct the roots that round most, the
+16-bit kernels take them as FP32 rounds them."""
 import numpy as np
 import pytest
 
