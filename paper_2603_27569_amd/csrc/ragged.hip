@@ -431,7 +431,7 @@ extern "C" int fft_plan_ragged(fft_ragged_plan_t* plan, const int64_t* sizes, in
     return hip_fail(e);
   }
   Layout layout = lay_out(p->class_count, p->shape_of_class, cus);
-  if (!named[5]) {
+  if (!named[5] && p->class_count[5] > 0) {
     // The two shapes of 8192 points cost about the same per transform, but A
     // takes two of them in a task: whichever grain the batch finishes earlier
     // with.  us on an MI355X, rows from HBM, A / B: 850 lengths 18.7 / 18.6, 1000
